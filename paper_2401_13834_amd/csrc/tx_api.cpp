@@ -20,9 +20,13 @@ tx_status from_hip(hipError_t e) { return tx::status_of(e); }
 void release_device(tx_plan_s* p) {
     if (p->d_dT) (void)hipFree(p->d_dT);
     if (p->d_rT) (void)hipFree(p->d_rT);
+    if (p->d_cT) (void)hipFree(p->d_cT);
+    if (p->d_rTo) (void)hipFree(p->d_rTo);
     if (p->d_mask) (void)hipFree(p->d_mask);
     p->d_dT = nullptr;
     p->d_rT = nullptr;
+    p->d_cT = nullptr;
+    p->d_rTo = nullptr;
     p->d_mask = nullptr;
     p->on_device = false;
 }
@@ -32,10 +36,32 @@ tx_status upload(tx_plan_s* p) {
     if (hipGetDevice(&dev) != hipSuccess) return TX_EDEVICE;
     const size_t n1 = p->dT.size() * sizeof(int32_t);
     const size_t n2 = p->rT.size() * sizeof(int32_t);
+    // The matrix-core first stage starts each series D(c_j, f_s) & 15 elements
+    // early: its delays of the sub-bands, and the fine offsets that go with it.
+    std::vector<int32_t> cT, rTo;
+    try {
+        cT.resize(static_cast<size_t>(p->nsub) * p->gpad);
+        rTo = p->rT;
+    } catch (const std::bad_alloc&) {
+        return TX_ENOMEM;
+    }
+    for (int32_t s = 0; s < p->nsub; ++s) {
+        for (int32_t j = 0; j < p->gpad; ++j)
+            cT[static_cast<size_t>(s) * p->gpad + j] =
+                p->coarse_sub[static_cast<size_t>(std::min(j, p->ngroups - 1)) * p->nsub + s];
+        for (int32_t i = 0; i < p->dpad; ++i)
+            rTo[static_cast<size_t>(s) * p->dpad + i] +=
+                cT[static_cast<size_t>(s) * p->gpad + std::min(i, p->ndm - 1) / p->g] & 15;
+    }
+    const size_t n3 = cT.size() * sizeof(int32_t);
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&p->d_dT), n1);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->d_rT), n2);
+    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->d_cT), n3);
+    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->d_rTo), n2);
     if (e == hipSuccess) e = hipMemcpy(p->d_dT, p->dT.data(), n1, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_rT, p->rT.data(), n2, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(p->d_cT, cT.data(), n3, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(p->d_rTo, rTo.data(), n2, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         release_device(p);
         return from_hip(e);
@@ -385,7 +411,7 @@ tx_status tx_tile_variant_info(int32_t stage, int32_t variant, int32_t* outputs_
     if (!outputs_per_tile || !trials_per_wave) return TX_EINVAL;
     if (stage == 1 && variant >= 0 && variant < tx::stage1_variant_count()) {
         const tx::Stage1Variant v = tx::stage1_variant(variant);
-        *outputs_per_tile = 256 * v.q;
+        *outputs_per_tile = v.tt;
         *trials_per_wave = v.jw;
         return TX_OK;
     }

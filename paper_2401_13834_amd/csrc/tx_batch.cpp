@@ -148,19 +148,34 @@ tx_status fill_box(const tx_batch_boxcar* box, tx::BoxcarArgs* a) {
     return TX_OK;
 }
 
+// Geometry of a job of `plan` with `nt` outputs among the kernels `have`
+// (null: any): the plan's tiles, or the general first stage where the library
+// chooses and `have` does not hold its choice.
+tx::DedispGeom job_geometry(const tx_plan_s* plan, int64_t nt, const Signature* have) {
+    const tx::Tiles t = tx::plan_tiles(plan);
+    const tx::DedispGeom g = tx::dedisp_geometry(plan, std::max<int64_t>(nt, 1), t);
+    if (!have || !g.ok || !tx::default_stage1(t) || have->lds1[static_cast<size_t>(g.tiles.s1)] >= g.lds1) return g;
+    return tx::general_geometry(plan, std::max<int64_t>(nt, 1), t);
+}
+
 // Kernels a job of `plan` with `nt` outputs (nw boxcar widths, 0 for none)
-// needs: its first- and second-stage classes and their LDS, its boxcar.
-tx_status job_needs(const tx_plan_s* plan, int64_t nt, int nw, Signature* need, tx::DedispGeom* geo_out) {
-    const tx::DedispGeom g = tx::dedisp_geometry(plan, std::max<int64_t>(nt, 1), tx::plan_tiles(plan));
+// needs: its first- and second-stage classes and their LDS, its boxcar.  With
+// no kernels given yet (`have` null) and the first stage left to the library, also the
+// general form, which any later job of a captured graph can take.
+tx_status job_needs(const tx_plan_s* plan, int64_t nt, int nw, Signature* need, const Signature* have) {
+    const tx::DedispGeom g = job_geometry(plan, nt, have);
     if (!g.ok) return TX_ENOTSUP;
     need->lds1[static_cast<size_t>(g.tiles.s1)] = std::max(need->lds1[static_cast<size_t>(g.tiles.s1)], g.lds1);
+    if (!have) {
+        const tx::DedispGeom o = tx::general_geometry(plan, std::max<int64_t>(nt, 1), tx::plan_tiles(plan));
+        if (o.ok) need->lds1[static_cast<size_t>(o.tiles.s1)] = std::max(need->lds1[static_cast<size_t>(o.tiles.s1)], o.lds1);
+    }
     const int c2 = s2_class(g.iw, g.tiles.s2);
     need->lds2[static_cast<size_t>(c2)] = std::max(need->lds2[static_cast<size_t>(c2)], g.lds2);
     if (nw > 0) {
         need->nwt = std::max(need->nwt, tx::boxcar_nwt(nw));
         need->ldsb = std::max(need->ldsb, tx::boxcar_tmax_bytes(need->nwt, nt));
     }
-    if (geo_out) *geo_out = g;
     return TX_OK;
 }
 
@@ -358,7 +373,8 @@ tx_status tx_batch_launch(tx_batch_t b, hipStream_t stream) {
     need.init();
     for (const Job& j : b->jobs) {
         const int64_t nt_cap = j.stream ? j.stream->max_block : j.nt;
-        const tx_status st = job_needs(j.plan, nt_cap, j.has_box ? j.box.nw : 0, &need, nullptr);
+        const tx_status st = job_needs(j.plan, nt_cap, j.has_box ? j.box.nw : 0, &need,
+                                       use_graph && b->exec ? &b->captured : nullptr);
         if (st != TX_OK) return st;
     }
     Signature sig;
@@ -387,7 +403,7 @@ tx_status tx_batch_launch(tx_batch_t b, hipStream_t stream) {
     int64_t scratch_need = 0;
     for (int k = 0; k < n; ++k) {
         Job& j = b->jobs[static_cast<size_t>(k)];
-        geo[static_cast<size_t>(k)] = tx::dedisp_geometry(j.plan, std::max<int64_t>(j.nt_out, 1), tx::plan_tiles(j.plan));
+        geo[static_cast<size_t>(k)] = job_geometry(j.plan, j.nt_out, &sig);
         if (!geo[static_cast<size_t>(k)].ok) return TX_ENOTSUP;
         if (j.nt_out > 0) {
             scratch_off[static_cast<size_t>(k)] = scratch_need;

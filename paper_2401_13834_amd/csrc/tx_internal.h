@@ -128,13 +128,17 @@ struct Stage1Args {
     int32_t x_off;          // first sample of every row at byte x_off (0..15) from x
     const uint8_t* mask;    // per channel, 0 = dropped (staged as zeros); null = keep all
     uint16_t* B;            // first-stage series [ngroups][nsub][B_pitch]
-    int64_t B_pitch;        // elements per series (multiple of the time tile)
+    int64_t B_pitch;        // elements per series
     const int32_t* dT;      // [nchan][gpad] D(c_j, f_ch), trial axis padded with the last group
     int32_t gpad;
     int32_t nchan, nsub, m, ngroups;
     int32_t n_jchunks;      // coarse-trial chunks per sub-band
-    int32_t n_ttiles;       // B_pitch / time tile
+    int32_t n_ttiles;       // time tiles
     int32_t lds_bytes;      // dynamic LDS per workgroup
+    // matrix-core form only:
+    const int32_t* cT;      // [nsub][gpad] D(c_j, f_s)
+    int32_t len;            // elements of a series the second stage uses (multiple of 16)
+    int32_t tiles_per_run;  // tiles a workgroup takes in turn (n_ttiles counts the runs)
 };
 
 struct Stage2Args {
@@ -143,7 +147,9 @@ struct Stage2Args {
     int32_t* Y;             // [ndm][y_pitch]
     int64_t y_pitch;
     int64_t nt;
-    const int32_t* rT;      // [nsub][dpad] D(dm_i, f_s) - D(c_j, f_s), trial axis padded
+    const int32_t* rT;      // [nsub][dpad] element of the series for output 0, trial axis padded:
+                            // D(dm_i, f_s) - D(c_j, f_s), plus D(c_j, f_s) & 15 after the
+                            // matrix-core first stage
     int32_t dpad;
     int32_t ndm, nsub, g, ngroups;
     int32_t n_ichunks;      // fine-trial chunks per group
@@ -254,10 +260,13 @@ struct NormGeom {
 
 // Tile variants (tx_kernels_dedisp.hip).  Stage 1: Q1 consecutive dwords (odd Q1, 4 outputs each)
 // per lane, JW coarse trials per wave, 4 waves sharing one time tile of
-// 256*Q1 outputs.  Stage 2: Q2 dwords (2 outputs each) per lane, the 4 waves
+// 256*Q1 outputs; mx: the matrix-core form (16 trials, Q1
+// output quads per lane and trial).  Stage 2: Q2 dwords (2 outputs each) per lane, the 4 waves
 // splitting a time tile of 512*Q2 outputs, IW fine trials per workgroup.
 struct Stage1Variant {
     int q, jw;
+    int tt;                 // outputs per tile
+    bool mx;                // the matrix-core form
 };
 struct Stage2Variant {
     int q;
@@ -269,6 +278,15 @@ Stage2Variant stage2_variant(int v);
 
 struct Tiles {
     int32_t s1 = -1, s1_lds = 0, s2 = -1, s2_lds = 0;   // -1 / 0: defaults
+};
+
+// What the matrix-core first stage makes of a plan, over runs of 16 coarse
+// trials (4 for the windows).
+struct MxShape {
+    int32_t spread = 0;     // largest spread of D(c_j,f) - D(c_j,f_s) in a channel
+    int32_t vspread_max = 0;   // largest spread of D(c_j,f_s) in a sub-band
+    double vspread = 0;     // its mean
+    double windows = 0;     // mean 16-byte windows per 4 channels and 4 trials
 };
 
 }  // namespace tx
@@ -290,12 +308,15 @@ struct tx_plan_s {
     bool on_device = false;
     int32_t* d_dT = nullptr;
     int32_t* d_rT = nullptr;
+    int32_t* d_cT = nullptr;           // [nsub][gpad] D(c_j, f_s)
+    int32_t* d_rTo = nullptr;          // rT + (D(c_j, f_s) & 15)
     uint8_t* d_mask = nullptr;         // per channel: 0 drops it from every sum (null: keep all)
     std::vector<uint8_t> mask;         // host copy (empty: keep all)
     mutable std::mutex mu;             // guards `tiles` and the spread cache
     tx::Tiles tiles;
     mutable std::vector<std::pair<int, int32_t>> spread1_cache;   // (J, spread)
     mutable std::vector<std::pair<int, int32_t>> spread2_cache;   // (IW, spread)
+    tx::MxShape mx;
 };
 
 struct tx_stream_s {
@@ -357,12 +378,17 @@ struct DedispGeom {
     Tiles tiles;            // resolved variants and LDS sizes
     int tt1, J1, tt2, iw;
     int64_t B_pitch;        // uint16 elements per first-stage series
+    int64_t len1;           // elements of a series the matrix-core first stage writes
+    int32_t run1;           // and its tiles per run
     int64_t ws_bytes;       // scratch bytes
     int32_t n_ttiles1, n_ttiles2, n_jchunks, n_ichunks;
     int32_t lds1, lds2;     // dynamic LDS per workgroup
     bool ok;                // false if some workgroup cannot fit its LDS rows
 };
 DedispGeom dedisp_geometry(const tx_plan_s* p, int64_t nt, const Tiles& want);
+bool default_stage1(const Tiles& t);       // the library chooses the first stage's variant
+// dedisp_geometry, but the general form where the library chooses.
+DedispGeom general_geometry(const tx_plan_s* p, int64_t nt, Tiles t);
 // Time-major [nt][tf_pitch] -> channel-major [nchan][ft_pitch] uint8
 // (tx_kernels_transpose.hip); pointers and pitches multiples of 16.
 hipError_t launch_transpose_tf(const uint8_t* d_tf, int64_t tf_pitch, int32_t nchan, int64_t nt, uint8_t* d_ft,

@@ -19,6 +19,20 @@
 
 namespace tx {
 
+// A wavefront's own LDS span: its LDS operations complete in order, so its
+// later reads see its earlier writes; the fence keeps the compiler from moving
+// them across each other.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+}  // namespace tx
+
+#include "tx_stage1_mx.h"
+
+namespace tx {
+
 __device__ __forceinline__ uint32_t perm_b32(uint32_t hi, uint32_t lo, uint32_t sel) {
     return __builtin_amdgcn_perm(hi, lo, sel);
 }
@@ -29,15 +43,6 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
     return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
-
-
-// A wavefront's own LDS span: its LDS operations complete in order, so its
-// later reads see its earlier writes; the fence keeps the compiler from moving
-// them across each other.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 // ---------------------------------------------------------------------------
 // Stage 1: B[j][s][u] = sum over ch in s of x[ch][u + D(c_j, f_ch)].
@@ -542,6 +547,32 @@ __global__ __launch_bounds__(kThreads) TX_S1B_WAVES(Q, JW) void stage1_batch_ker
     });
 }
 
+template <int QN>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void stage1_mx_kernel(Stage1Args a) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    int* red = reinterpret_cast<int*>(lds);   // block_max scratch, used before anything is staged
+    stage1_mx_tiles<QN>(a, xcd_tile(blockIdx.x, a.nsub * a.n_ttiles * a.n_jchunks), lds, red, threadIdx.x);
+}
+
+template <int QN>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void stage1_mx_batch_kernel(const Stage1Args* __restrict__ jobs,
+                                                                const int* __restrict__ prefix_base,
+                                                                const int* __restrict__ info, uint32_t* queue) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    int* red = reinterpret_cast<int*>(lds);
+    const int njobs = info[0];
+    if (njobs <= 0) return;
+    const Stage1Args* cj = jobs + info[1];
+    const int* prefix = prefix_base + info[2];
+    for_each_claimed(prefix[njobs], queue, [&](int t) {
+        const int jb = find_job(prefix, njobs, t);
+        const Stage1Args a = cj[jb];
+        int tv = static_cast<int>(threadIdx.x);
+        asm volatile("" : "+v"(tv));
+        stage1_mx_tiles<QN>(a, t - prefix[jb], lds, red, tv);
+    });
+}
+
 // The 16-trial, 3-dword variant is held to 4 waves per SIMD (128 VGPRs): left
 // alone it takes 131 and runs 3 waves; capped it keeps 3 dwords in scratch,
 // reloaded once per staging round.  Other variants are left to the compiler.
@@ -576,17 +607,28 @@ __global__ __launch_bounds__(kThreads) TX_S2_WAVES(IW, Q) void stage2_batch_kern
 // ---------------------------------------------------------------------------
 // Variants, geometry and launches.
 // ---------------------------------------------------------------------------
-static const Stage1Variant kS1[] = {{5, 4}, {7, 4}, {9, 4}, {5, 2}, {7, 2}, {9, 2}, {11, 2}, {13, 1}, {3, 4}};
+#define TX_S1V(Q, JW) {Q, JW, 256 * (Q), false}
+static const Stage1Variant kS1[] = {TX_S1V(5, 4), TX_S1V(7, 4), TX_S1V(9, 4), TX_S1V(5, 2), TX_S1V(7, 2),
+                                    TX_S1V(9, 2), TX_S1V(11, 2), TX_S1V(13, 1), TX_S1V(3, 4), {18, 4, 64 * 18, true}};
+#undef TX_S1V
 static const Stage2Variant kS2[] = {{1}, {3}, {5}};
 constexpr int kNS1 = sizeof(kS1) / sizeof(kS1[0]);
 constexpr int kNS2 = sizeof(kS2) / sizeof(kS2[0]);
 constexpr int kDefaultLds = 27296;        // first stage: a sixth of a CU's LDS (94 VGPRs hold it to 5 per CU)
 constexpr int kDefaultLds2 = 32 * 1024;   // second stage
-// Defaults: the fastest pair on the 4096-channel paper-scale block (first
+// Defaults: first stage the matrix-core form (mx_pays); otherwise, and for the
+// second stage, the fastest on the 4096-channel paper-scale block (general first
 // stage 9 output dwords per lane x 4 trials per wavefront at 27296 bytes, second
 // stage 3 output dwords per lane at 32 KB); tx_plan_autotune measures per
 // plan.  Q is odd in both stages (bank-conflict-free lane stride).
 constexpr int kDefaultS1 = 2;
+constexpr int kDefaultMx = 9;
+// Tiles that a matrix-core workgroup takes in turn (its tables are built once
+// and rows are loaded from one tile to the next): up to 8, while the launch
+// keeps at least 2 workgroups per resident one.  On the paper-scale block runs of 4, 8
+// and 16 tiles measured within 2%.
+constexpr int kMxMinRuns = 2048;
+constexpr int kDefaultLdsMx = 40 * 1024;   // matrix-core form: a quarter of a CU's LDS (its registers hold 4 workgroups)
 constexpr int kDefaultS2 = 1;
 
 int stage1_variant_count() { return kNS1; }
@@ -614,14 +656,56 @@ static int pick_iw(int32_t g) {
     return best;
 }
 
+// Least LDS of a first-stage workgroup: one staged row (four in the matrix-core
+// form) and the shift tables, or the output pass.
+static int stage1_need(const tx_plan_s* p, const Stage1Variant& v) {
+    if (v.mx) {
+        const int row = (p->mx.spread + 15 + v.tt + 35) & ~15;
+        const int64_t need = 4ll * row + kMxTabBytes * ((p->m + 3) & ~3) + kMxOneHot + kMxPad + 16;
+        return static_cast<int>(std::min<int64_t>(need, INT32_MAX));
+    }
+    const int J = 4 * v.jw;
+    const int sp1 = plan_spread1(p, J) + 15;
+    const int W1 = ((sp1 >> 2) + 64 * v.q + 1 + 3) & ~3;
+    const int tabs1 = (p->m * (J + 1) * 4 + 15) & ~15;                            // shift tables
+    return std::max(4 * W1 + tabs1 + 48, kWaves * 512 * v.q);   // a row and the tables; output pass
+}
+
+// Sizes that the matrix-core form holds: shifts in 15 bits, times in 32, the
+// rows of 4 trials within a buffer resource, its staged rows in LDS.
+static bool mx_fits(const tx_plan_s* p, int64_t nt) {
+    return p->mx.spread < 16384 && nt + p->overlap + 2 * p->max_extent + 65536 < INT32_MAX &&
+           8 * p->nsub * (nt + p->max_extent + 65536) < INT32_MAX && stage1_need(p, kS1[kDefaultMx]) <= device_max_lds();
+}
+
+// Default first stage: the matrix-core form unless its extra work outweighs
+// it.  Its matrix products grow with the windows of the plan (DM steps whose
+// delays spread 4 trials over more than 16 samples) and with the trials that
+// fill up the last 16, and few channels per sub-band leave its tables and
+// output pass to be paid by few products.  Measured over 54 plans, blocks of
+// 4096 to 49152 samples (its time of the first stage over the general form's):
+// estimates of 1.1-1.4 0.32-0.73, 1.5-2.0 0.52-0.90, 2.0-3.3 0.36-1.07 (mean
+// 0.80), 3.5-4.7 0.83-1.48 (mean 1.12), above 1.02-2.25.  The plan alone
+// decides, so that scratch sized for a long block serves shorter ones.
+static bool mx_pays(const tx_plan_s* p) {
+    const double padded = static_cast<double>((p->ngroups + 15) / 16 * 16) / p->ngroups;
+    return p->mx.windows * padded * (1.0 + 5.0 / p->m) < 3.4;
+}
+
+bool default_stage1(const Tiles& t) { return t.s1 < 0 || t.s1 >= kNS1; }
+
 DedispGeom dedisp_geometry(const tx_plan_s* p, int64_t nt, const Tiles& want) {
     DedispGeom g{};
     g.tiles = want;
-    if (g.tiles.s1 < 0 || g.tiles.s1 >= kNS1) g.tiles.s1 = kDefaultS1;
+    if (default_stage1(g.tiles)) {
+        // (a plan that the general form refuses stays refused)
+        const bool general = stage1_need(p, kS1[kDefaultS1]) <= device_max_lds();
+        g.tiles.s1 = general && mx_fits(p, nt) && mx_pays(p) ? kDefaultMx : kDefaultS1;
+    }
     if (g.tiles.s2 < 0 || g.tiles.s2 >= kNS2) g.tiles.s2 = kDefaultS2;
     const Stage1Variant v1 = kS1[g.tiles.s1];
     const Stage2Variant v2 = kS2[g.tiles.s2];
-    g.tt1 = 256 * v1.q;
+    g.tt1 = v1.tt;
     g.J1 = 4 * v1.jw;
     g.tt2 = 512 * v2.q;
     g.iw = pick_iw(p->g);
@@ -629,11 +713,9 @@ DedispGeom dedisp_geometry(const tx_plan_s* p, int64_t nt, const Tiles& want) {
 
     // LDS: at least one row (and its table) per workgroup; stage 1 double
     // buffers when two fit in its LDS size.
-    const int sp1 = plan_spread1(p, g.J1) + 15;
-    const int W1 = ((sp1 >> 2) + 64 * v1.q + 1 + 3) & ~3;
-    const int tabs1 = (p->m * (g.J1 + 1) * 4 + 15) & ~15;                            // shift tables
-    const int need1 = std::max(4 * W1 + tabs1 + 48, kWaves * 512 * v1.q);   // a row and the tables; output pass
-    g.lds1 = std::max(g.tiles.s1_lds > 0 ? g.tiles.s1_lds : kDefaultLds, need1);
+    const int need1 = stage1_need(p, v1);
+    const int def1 = v1.mx ? kDefaultLdsMx : kDefaultLds;
+    g.lds1 = std::max(g.tiles.s1_lds > 0 ? g.tiles.s1_lds : def1, need1);
     const int sp2 = plan_spread2(p, g.iw) + 7;
     const int W2 = ((sp2 >> 1) + 256 * v2.q + 1 + 3) & ~3;
     const int tabs2 = ((p->nsub + 3) & ~3) * iwp * 4;                                // shift table
@@ -642,7 +724,7 @@ DedispGeom dedisp_geometry(const tx_plan_s* p, int64_t nt, const Tiles& want) {
     const int max_lds = device_max_lds();
     g.lds1 = std::min(g.lds1, std::max(need1, max_lds));
     g.lds2 = std::min(g.lds2, std::max(need2, max_lds));
-    g.ok = g.lds1 <= max_lds && g.lds2 <= max_lds;
+    g.ok = g.lds1 <= max_lds && g.lds2 <= max_lds && (!v1.mx || mx_fits(p, nt));
     g.tiles.s1_lds = g.lds1;
     g.tiles.s2_lds = g.lds2;
 
@@ -651,8 +733,21 @@ DedispGeom dedisp_geometry(const tx_plan_s* p, int64_t nt, const Tiles& want) {
     // holds one 16-byte piece more than the W dwords the trials read), start
     // <= last tile start + max extent.
     const int64_t need = static_cast<int64_t>(std::max(g.n_ttiles2 - 1, 0)) * g.tt2 + p->max_extent + 2 * W2 + 8;
-    g.B_pitch = round_up(std::max<int64_t>(need, nt + p->max_extent), g.tt1);
-    g.n_ttiles1 = static_cast<int32_t>(g.B_pitch / g.tt1);
+    if (v1.mx) {
+        // Series start up to 15 elements early; tiles are cut at multiples of
+        // their length of v = u + D(c_j, f_s), which a sub-band's trials
+        // start at different points of.
+        g.len1 = round_up(nt + p->max_extent + 15, 16);
+        g.B_pitch = round_up(std::max<int64_t>(need + 15, g.len1), 16);
+        const auto tiles = [&](double spread) { return static_cast<int64_t>((g.len1 + spread + 15) / g.tt1) + 2; };
+        const int64_t all = tiles(p->mx.vspread) * p->nsub * ((p->ngroups + g.J1 - 1) / g.J1);   // about
+        g.run1 = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(all / kMxMinRuns, 8)));
+        g.n_ttiles1 = static_cast<int32_t>((tiles(p->mx.vspread_max) + g.run1 - 1) / g.run1);
+    } else {
+        g.len1 = 0;
+        g.B_pitch = round_up(std::max<int64_t>(need, nt + p->max_extent), g.tt1);
+        g.n_ttiles1 = static_cast<int32_t>(g.B_pitch / g.tt1);
+    }
     g.n_jchunks = (p->ngroups + g.J1 - 1) / g.J1;
     g.n_ichunks = (p->g + g.iw - 1) / g.iw;
     g.ws_bytes = round_up(static_cast<int64_t>(p->ngroups) * p->nsub * g.B_pitch * 2, 256);
@@ -694,9 +789,11 @@ struct KernelPair {
     const void* batch;
 };
 #define TX_S1(Q, JW) {reinterpret_cast<const void*>(&stage1_kernel<Q, JW>), reinterpret_cast<const void*>(&stage1_batch_kernel<Q, JW>)}
+#define TX_S1MX(QN) {reinterpret_cast<const void*>(&stage1_mx_kernel<QN>), reinterpret_cast<const void*>(&stage1_mx_batch_kernel<QN>)}
 static const KernelPair kS1Fn[kNS1] = {TX_S1(5, 4), TX_S1(7, 4), TX_S1(9, 4), TX_S1(5, 2), TX_S1(7, 2),
-                                        TX_S1(9, 2), TX_S1(11, 2), TX_S1(13, 1), TX_S1(3, 4)};
+                                        TX_S1(9, 2), TX_S1(11, 2), TX_S1(13, 1), TX_S1(3, 4), TX_S1MX(18)};
 #undef TX_S1
+#undef TX_S1MX
 static const int kIW[] = {16, 13, 8, 4, 2, 1};
 constexpr int kNIW = 6;
 #define TX_S2(IW, Q) {reinterpret_cast<const void*>(&stage2_kernel<IW, Q>), reinterpret_cast<const void*>(&stage2_batch_kernel<IW, Q>)}
@@ -736,13 +833,16 @@ void fill_stage_args(const tx_plan_s* p, const DedispGeom& geo, const uint8_t* d
     s1->n_jchunks = geo.n_jchunks;
     s1->n_ttiles = geo.n_ttiles1;
     s1->lds_bytes = geo.lds1;
+    s1->cT = p->d_cT;
+    s1->len = static_cast<int32_t>(geo.len1);
+    s1->tiles_per_run = geo.run1;
     *s2 = Stage2Args{};
     s2->B = d_B;
     s2->B_pitch = geo.B_pitch;
     s2->Y = d_out;
     s2->y_pitch = out_pitch;
     s2->nt = nt;
-    s2->rT = p->d_rT;
+    s2->rT = kS1[geo.tiles.s1].mx ? p->d_rTo : p->d_rT;
     s2->dpad = p->dpad;
     s2->ndm = p->ndm;
     s2->nsub = p->nsub;
@@ -835,6 +935,11 @@ hipError_t launch_stage2_batch(int iw, int variant, int lds, const BatchRefs& r,
 
 int stage2_iw(int32_t g) { return pick_iw(g); }
 
+DedispGeom general_geometry(const tx_plan_s* p, int64_t nt, Tiles t) {
+    if (default_stage1(t)) t.s1 = kDefaultS1;
+    return dedisp_geometry(p, nt, t);
+}
+
 // ---------------------------------------------------------------------------
 // Dedispersion without allocation.  The first-stage series of one chunk of
 // output samples live in `scratch`, a file-scope device array that every GPU
@@ -888,12 +993,13 @@ hipError_t launch_dedisperse_noalloc(const tx_plan_s* p, const Tiles& want, cons
                                      int64_t* need_bytes) {
     *need_bytes = 0;
     const int64_t cap = TX_NOALLOC_SCRATCH_BYTES;
-    // The plan's tiles, else the first-stage variant (second stage kept) that
+    // The plan's tiles, else the general first-stage variant (second stage kept) that
     // gives the longest chunk: a shorter first-stage tile shortens the series.
     Tiles best = want;
     int64_t chunk = largest_chunk(p, nt, want, cap);
     if (chunk < nt) {
         for (int v = 0; v < kNS1; ++v) {
+            if (kS1[v].mx) continue;
             Tiles t = want;
             t.s1 = v;
             t.s1_lds = 0;
@@ -907,6 +1013,7 @@ hipError_t launch_dedisperse_noalloc(const tx_plan_s* p, const Tiles& want, cons
     if (chunk <= 0) {
         int64_t smallest = INT64_MAX;
         for (int v = 0; v < kNS1; ++v) {
+            if (kS1[v].mx) continue;
             Tiles t = want;
             t.s1 = v;
             t.s1_lds = 0;

@@ -74,6 +74,46 @@ static int32_t choose_nsub(const std::vector<double>& f, int32_t ndm) {
     return best;
 }
 
+static MxShape mx_shape(const tx_plan_s* p) {
+    MxShape x;
+    const size_t S = static_cast<size_t>(p->nsub);
+    int64_t vs = 0, windows = 0, nv = 0, nw = 0;
+    for (int32_t s = 0; s < p->nsub; ++s) {
+        std::vector<int32_t> cs(p->ngroups);
+        for (int32_t j = 0; j < p->ngroups; ++j) cs[j] = p->coarse_sub[j * S + s];
+        for (int32_t j0 = 0; j0 < p->ngroups; j0 += 16) {
+            const int32_t jn = std::min(j0 + 16, p->ngroups);
+            vs += cs[jn - 1] - cs[j0];
+            x.vspread_max = std::max(x.vspread_max, cs[jn - 1] - cs[j0]);
+            ++nv;
+            for (int32_t c0 = 0; c0 < p->m; c0 += 4) {
+                int32_t most[4] = {0, 0, 0, 0};       // per 4 trials, the largest spread of the 4 channels
+                for (int32_t c = c0; c < std::min(c0 + 4, p->m); ++c) {
+                    const int32_t* dt = p->dT.data() + static_cast<size_t>(s * p->m + c) * p->gpad;
+                    int32_t lo = INT32_MAX, hi = INT32_MIN;
+                    for (int32_t j4 = j0; j4 < jn; j4 += 4) {
+                        int32_t l4 = INT32_MAX, h4 = INT32_MIN;
+                        for (int32_t j = j4; j < std::min(j4 + 4, jn); ++j) {
+                            const int32_t d = dt[j] - cs[j];
+                            l4 = std::min(l4, d);
+                            h4 = std::max(h4, d);
+                        }
+                        lo = std::min(lo, l4);
+                        hi = std::max(hi, h4);
+                        most[(j4 - j0) / 4] = std::max(most[(j4 - j0) / 4], h4 - l4);
+                    }
+                    x.spread = std::max(x.spread, hi - lo);
+                }
+                for (int32_t g = 0; g < (jn - j0 + 3) / 4; ++g) windows += 1 + (most[g] + 1 + 7) / 16;
+                nw += (jn - j0 + 3) / 4;
+            }
+        }
+    }
+    x.vspread = static_cast<double>(vs) / static_cast<double>(nv);
+    x.windows = static_cast<double>(windows) / static_cast<double>(nw);
+    return x;
+}
+
 tx_status build_plan_host(const double* freqs, int32_t nchan, double tsamp, const double* dms,
                           int32_t ndm, int32_t nsub, int32_t dms_per_group, tx_plan_s* p) {
     if (!freqs || !dms || nchan < 1 || ndm < 1 || nsub < 0 || dms_per_group < 0) return TX_EINVAL;
@@ -138,15 +178,11 @@ tx_status build_plan_host(const double* freqs, int32_t nchan, double tsamp, cons
             max_ext = std::max<int64_t>(max_ext, r);
         }
     }
-    for (int32_t i = 0; i < ndm; ++i) {
-        int32_t j = i / g;
-        for (int32_t ch = 0; ch < nchan; ++ch) {
-            int32_t s = ch / m;
-            int64_t off = static_cast<int64_t>(p->coarse_chan[static_cast<size_t>(j) * nchan + ch]) +
-                          p->rel[static_cast<size_t>(i) * nsub + s];
-            max_off = std::max(max_off, off);
-        }
-    }
+    // (a group's first trial is its coarse one: extent is the largest rel)
+    for (int32_t j = 0; j < G; ++j)
+        for (int32_t ch = 0; ch < nchan; ++ch)
+            max_off = std::max(max_off, static_cast<int64_t>(p->coarse_chan[static_cast<size_t>(j) * nchan + ch]) +
+                                            p->extent[static_cast<size_t>(j) * nsub + ch / m]);
     p->max_extent = max_ext;
     p->overlap = std::max(max_off, reach);
 
@@ -164,6 +200,7 @@ tx_status build_plan_host(const double* freqs, int32_t nchan, double tsamp, cons
     for (int32_t s = 0; s < nsub; ++s)
         for (int32_t i = 0; i < p->dpad; ++i)
             p->rT[static_cast<size_t>(s) * p->dpad + i] = p->rel[static_cast<size_t>(std::min(i, ndm - 1)) * nsub + s];
+    p->mx = mx_shape(p);
     return TX_OK;
 }
 
