@@ -8,10 +8,9 @@
 //    as differences) of its 4096 + longest-width samples go to LDS; the same
 //    loads accumulate the exact moments sum y and sum y^2 (uint64);
 //  * per width, every lane keeps the largest window sum of its 16 starts; the
-//    wavefront's largest is compared with the wavefront's best so far, and
-//    only when it beats it (a few tiles per row) does the wavefront look up
-//    the earliest start reaching it; the workgroup's largest sum per (tile,
-//    width) is kept in LDS.
+//    tile's largest is compared with the row's best so far, and only when it
+//    beats it (a few tiles per row) is the earliest start reaching it looked
+//    up; the largest sum per (tile, width) is kept in LDS.
 // Then c = floor(sum/T), Q = sum y^2 - 2 c sum + T c^2 (= sum (y - c)^2, mod
 // 2^64), var = Q/T - (r/T)^2, sigma and 1/(sigma T) in float64 give the peak
 // S/N, and per width the least window sum S* whose S/N reaches gamma
@@ -43,11 +42,12 @@ struct BoxShared {
     double inv_d;
     long long sum;
     int state;
-    int32_t wS[kWaves][NWT];       // per wavefront: best sum per width so far, and
-    int32_t wT[kWaves][NWT];       // its earliest start
+    __align__(16) int32_t wS[NWT][kWaves];   // the tile's largest sum per width and wavefront, and where
+    __align__(16) int32_t wT[NWT][kWaves];   // it is the row's new best, its earliest start
+    int32_t bS[NWT], bT[NWT];                // per width: the row's largest sum so far and its earliest start
 };
 
-extern __shared__ int32_t tx_box_tmax[];   // [tiles][NWT]: workgroup's largest sum per tile and width
+extern __shared__ int32_t tx_box_tmax[];   // [tiles][NWT]: workgroup's largest sum per tile (from its first) and width
 
 __device__ __forceinline__ double snr_of(int64_t T, int64_t S, int64_t w, int64_t sum, double inv_d, double rsw) {
     const int64_t N = T * S - w * sum;
@@ -186,16 +186,24 @@ __device__ __forceinline__ void scan_tile(const TX_GLOBAL int32_t* __restrict__ 
 // (j < 16), so a wavefront reads 64 consecutive LDS words per load (no bank
 // conflicts for any width).  TAIL: some windows reach past the row end.  Width
 // slots past the row's widths repeat its last width.
+//
+// First every wavefront's largest sums of all widths; then, where the tile
+// beats the row's best sum of a width (a few tiles per row), the wavefronts
+// that hold that sum look up its earliest start.  Comparing with the whole
+// row's best, and not each wavefront with its own, leaves a quarter of the
+// lookups, and each costs about as much as a width's sums.  The widths are a
+// rolled loop, two a turn: a row's code is a third of the unrolled one's.
+// 4096 rows of 65536 samples, 10 widths: 521 us with lookups per wavefront and
+// unrolled widths, 365 so (1.07 GB: 2.9 TB/s); 96 rows of 1000003 samples 1340 and 1100.
 template <int NWT, bool TAIL>
 __device__ __forceinline__ void peak_tile(const BoxcarArgs& a, BoxShared<NWT>& sh, int tile, int t0, int tid,
                                           bool keep_tmax) {
-    const int wave = tid >> 6;
+    const int wave = tid >> 6, lane = tid & 63;
     const int T = a.nt;
     uint32_t Pt[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) Pt[j] = sh.P[tid + 256 * j];
-    int32_t tm[NWT];
-#pragma unroll
+#pragma unroll 1
     for (int i = 0; i < NWT; i += 2) {
         // Per-width values come from LDS, which keeps the registers free.
         const int w0 = sh.wd[i], w1 = sh.wd[i + 1];
@@ -210,87 +218,110 @@ __device__ __forceinline__ void peak_tile(const BoxcarArgs& a, BoxShared<NWT>& s
             tm0 = max(tm0, (!TAIL || t + w0 <= T) ? S0 : INT32_MIN);   // no window past the row end
             tm1 = max(tm1, (!TAIL || t + w1 <= T) ? S1 : INT32_MIN);
         }
-        tm[i] = tm0;
-        tm[i + 1] = tm1;
-        // Keep each width pair's LDS reads next to their arithmetic.
-        __builtin_amdgcn_sched_barrier(0);
+        const int32_t m0 = wave_max_i32(tm0), m1 = wave_max_i32(tm1);
+        if (lane < 2) sh.wS[i + lane][wave] = lane == 0 ? m0 : m1;
     }
-    // Wavefront maxima of all widths (independent reductions, interleaved).
-    int32_t wm[NWT];
+    __syncthreads();
+    // Lane i: width i.
+    int32_t M = INT32_MIN;
+    unsigned long long look = 0;
+    if (lane < NWT) {
+        const int4 q = *reinterpret_cast<const int4*>(sh.wS[lane]);
+        M = max(max(q.x, q.y), max(q.z, q.w));
+        if (keep_tmax && wave == 0) tx_box_tmax[tile * NWT + lane] = M;
+        look = M > sh.bS[lane];
+    }
+    const unsigned long long rec = __ballot(look);            // widths with a new best: the same in every wavefront
+    if (rec == 0) return;
+    for (unsigned long long left = __ballot(look && sh.wS[lane < NWT ? lane : 0][wave] == M); left; left &= left - 1) {
+        const int i = __builtin_ctzll(left);
+        const int32_t m = __builtin_amdgcn_readlane(M, i);
+        const int w = sh.wd[i];
+        const uint32_t* p = sh.P + tid + w;
+        int32_t first = INT32_MAX;
 #pragma unroll
-    for (int i = 0; i < NWT; ++i) wm[i] = wave_max_i32(tm[i]);
-#pragma unroll 1
-    for (int ii = 0; ii < NWT; ++ii) {
-        // wm[ii] with a run-time ii: select among the (uniform) values.
-        int32_t m = wm[0];
-#pragma unroll
-        for (int k = 1; k < NWT; ++k) m = (k == ii) ? wm[k] : m;
-        if (keep_tmax && (tid & 63) == 0) atomicMax(&tx_box_tmax[tile * NWT + ii], m);
-        if (m > sh.wS[wave][ii]) {                      // wavefront-uniform, a few tiles per row
-            const int w = sh.wd[ii];
-            int32_t first = INT32_MAX;
-#pragma unroll 1
-            for (int j = 15; j >= 0; --j) {             // rolled: this path is rare
-                const int e = tid + 256 * j;
-                const int t = t0 + e;
-                const int32_t S = static_cast<int32_t>(sh.P[e + w] - sh.P[e]);
-                first = ((!TAIL || t + w <= T) && S == m) ? t : first;
-            }
-            const int32_t ft = wave_min_i32(first);
-            if ((tid & 63) == 0) {
-                sh.wS[wave][ii] = m;
-                sh.wT[wave][ii] = ft;
-            }
+        for (int j = 15; j >= 0; --j) {
+            const int t = t0 + tid + 256 * j;
+            const int32_t S = static_cast<int32_t>(p[256 * j] - Pt[j]);
+            first = ((!TAIL || t + w <= T) && S == m) ? t : first;
         }
+        const int32_t ft = wave_min_i32(first);
+        if (lane == 0) sh.wT[i][wave] = ft;
+    }
+    __syncthreads();
+    if (wave == 0 && look) {
+        int32_t t = INT32_MAX;
+#pragma unroll
+        for (int v = 0; v < kWaves; ++v)
+            if (sh.wS[lane][v] == M) t = min(t, sh.wT[lane][v]);
+        sh.bS[lane] = M;
+        sh.bT[lane] = t;
     }
 }
 
 // Candidates of one tile (rare: only tiles where some width's largest sum
-// reaches its threshold S*).  Widths increase, so a strict ">" keeps the
-// smaller width on equal S/N.
+// reaches its threshold S*).  The starts that pass are found first, as 16 bits
+// per lane, with the sums alone; the wavefront then takes its places in the
+// list with one atomic, and only the starts that pass have their S/N worked
+// out.  (One atomic per 64 starts and the S/N of every start and width had
+// made a tile with candidates cost as much as ten without.)  Widths increase,
+// so a strict ">" keeps the smaller width on equal S/N.
 template <int NWT>
-__device__ __forceinline__ void cand_tile(const BoxcarArgs& a, BoxShared<NWT>& sh, int row, int t0, long long sum,
-                                          double inv_d, int tid) {
+__device__ __forceinline__ void cand_tile(const BoxcarArgs& a, BoxShared<NWT>& sh, int row, int tile, bool keep_tmax,
+                                          long long sum, double inv_d, int tlo, int tid) {
     const int T = a.nt;
+    const int t0 = tile * kBoxTile;
+    uint32_t pass = 0;
 #pragma unroll 1
-    for (int j = 0; j < 16; ++j) {
-        const int e = tid + 256 * j;
-        const int t = t0 + e;
+    for (int i = 0; i < a.ne; ++i) {
+        const int32_t thr = max(sh.sthr[i], 0);           // window sums are >= 0
+        if (keep_tmax && tx_box_tmax[(tile - tlo) * NWT + i] < thr) continue;      // workgroup-uniform
+        const int w = sh.wd[i];
+        const int lim = T - w - t0 - tid;                 // starts with 256 j <= lim have their window in the row
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int32_t S = static_cast<int32_t>(sh.P[tid + 256 * j + w] - sh.P[tid + 256 * j]);
+            pass |= S >= thr && 256 * j <= lim ? 1u << j : 0u;
+        }
+    }
+    const uint32_t n = __popc(pass);
+    const uint32_t incl = wave_incl_sum(n);
+    const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+    if (total == 0) return;
+    unsigned long long base = 0;
+    if ((tid & 63) == 0) base = atomicAdd(a.count, static_cast<unsigned long long>(total));
+    base = __shfl(base, 0);
+    unsigned long long slot = base + (incl - n);
+#pragma unroll 1
+    for (; pass; pass &= pass - 1, ++slot) {
+        if (static_cast<long long>(slot) >= a.cap) break;
+        const int e = tid + 256 * (__ffs(pass) - 1);
         const uint32_t pt = sh.P[e];
-        bool pass = false;
         double bs = 0.0;
         int bw = -1;
+#pragma unroll 1
         for (int i = 0; i < a.ne; ++i) {
             const int w = sh.wd[i];
-            if (t + w > T) continue;
+            if (t0 + e + w > T) break;
             const int32_t S = static_cast<int32_t>(sh.P[e + w] - pt);
-            pass = pass || S >= max(sh.sthr[i], 0);       // window sums are >= 0
             const double sn = snr_of(T, S, w, sum, inv_d, sh.rs[i]);
             if (bw < 0 || sn > bs) {
                 bs = sn;
                 bw = w;
             }
         }
-        if (!pass) continue;
-        const unsigned long long slot = atomicAdd(a.count, 1ull);
-        if (static_cast<long long>(slot) < a.cap) {
-            tx_cand c;
-            c.dm_index = row;
-            c.width = bw;
-            c.time = t;
-            c.snr = bs;
-            to_global(a.cands)[slot] = c;
-        }
+        tx_cand c;
+        c.dm_index = row;
+        c.width = bw;
+        c.time = t0 + e;
+        c.snr = bs;
+        to_global(a.cands)[slot] = c;
     }
 }
 
-// Widths and 1/sqrt(w) of the row's job into LDS, the wavefronts' per-width
-// best cleared, and the per-(tile, width) maxima table reset.
+// Widths and 1/sqrt(w) of the row's job into LDS, the per-width best cleared.
 template <int NWT>
-__device__ __forceinline__ void row_setup(const BoxcarArgs& a, int ntiles, bool keep_tmax, BoxShared<NWT>& sh,
-                                          int tid) {
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
+__device__ __forceinline__ void row_setup(const BoxcarArgs& a, BoxShared<NWT>& sh, int tid) {
     if (tid < NWT) {
         int32_t w = 0;
         double r = 0.0;
@@ -302,22 +333,14 @@ __device__ __forceinline__ void row_setup(const BoxcarArgs& a, int ntiles, bool 
             }
         sh.wd[tid] = w;
         sh.rs[tid] = r;
+        sh.bS[tid] = INT32_MIN;
+        sh.bT[tid] = 0;
     }
-    if (lane == 0) {
-#pragma unroll
-        for (int i = 0; i < NWT; ++i) {
-            sh.wS[wave][i] = INT32_MIN;
-            sh.wT[wave][i] = 0;
-        }
-    }
-    if (keep_tmax)
-        for (int k = tid; k < ntiles * NWT; k += kThreads) tx_box_tmax[k] = INT32_MIN;
     __syncthreads();
 }
 
 // Tiles [tlo, thi) of a row: running sums, exact moments (wavefront sums left
-// in sh.red*), per-width best of every wavefront (sh.wS / sh.wT) and the
-// per-(tile, width) maxima.
+// in sh.red*), per-width best (sh.bS / sh.bT) and the per-(tile, width) maxima.
 template <int NWT>
 __device__ __forceinline__ void row_scan(const BoxcarArgs& a, int tlo, int thi, bool keep_tmax,
                                          const TX_GLOBAL int32_t* __restrict__ y, bool vec, BoxShared<NWT>& sh,
@@ -336,8 +359,8 @@ __device__ __forceinline__ void row_scan(const BoxcarArgs& a, int tlo, int thi, 
         asm volatile("" : "+v"(tv));
         scan_tile<true>(y, T, t0, L, sh.P, sh.wtot, vec, tv, m);
         if (a.ne > 0) {
-            if (t0 + kBoxTile + a.wmax > T) peak_tile<NWT, true>(a, sh, tile, t0, tv, keep_tmax);
-            else peak_tile<NWT, false>(a, sh, tile, t0, tv, keep_tmax);
+            if (t0 + kBoxTile + a.wmax > T) peak_tile<NWT, true>(a, sh, tile - tlo, t0, tv, keep_tmax);
+            else peak_tile<NWT, false>(a, sh, tile - tlo, t0, tv, keep_tmax);
         }
         __syncthreads();
     }
@@ -352,10 +375,10 @@ __device__ __forceinline__ void row_scan(const BoxcarArgs& a, int tlo, int thi, 
     __syncthreads();
 }
 
-// Statistics, the row's peak and (when asked) its candidates, from the state
-// row_scan left in LDS.
+// Statistics, the row's peak (when `peak`) and (when asked) the candidates of
+// its tiles [tlo, thi), from the state row_scan left in LDS.
 template <int NWT>
-__device__ __forceinline__ void row_finish(const BoxcarArgs& a, int row, int ntiles, bool keep_tmax,
+__device__ __forceinline__ void row_finish(const BoxcarArgs& a, int row, bool peak, int tlo, int thi, bool keep_tmax,
                                            const TX_GLOBAL int32_t* __restrict__ y, bool vec, BoxShared<NWT>& sh,
                                            int tid) {
     const int T = a.nt;
@@ -396,7 +419,7 @@ __device__ __forceinline__ void row_finish(const BoxcarArgs& a, int row, int nti
     const double inv_d = sh.inv_d;
     const long long sum = sh.sum;
     if (state != 0) {
-        if (tid == 0 && a.want_peaks) {
+        if (tid == 0 && peak) {
             to_global(a.snr)[row] = state == 1 ? 0.0 : __builtin_nan("");
             to_global(a.width)[row] = state == 1 ? a.w_first : -1;
             to_global(a.time)[row] = state == 1 ? 0 : -1;
@@ -405,34 +428,33 @@ __device__ __forceinline__ void row_finish(const BoxcarArgs& a, int row, int nti
         return;
     }
 
-    // ---- peak: (largest S, earliest t) per width, then the best width -------------
-    if (a.want_peaks && tid == 0) {
-        double bs = 0.0;
-        int bw = -1;
-        long long bt = 0;
-        for (int i = 0; i < a.ne; ++i) {
-            const int w = sh.wd[i];
-            int32_t S = sh.wS[0][i], t = sh.wT[0][i];
-            for (int v = 1; v < kWaves; ++v)
-                if (sh.wS[v][i] > S || (sh.wS[v][i] == S && sh.wT[v][i] < t)) {
-                    S = sh.wS[v][i];
-                    t = sh.wT[v][i];
-                }
-            const double sn = snr_of(T, S, w, sum, inv_d, sh.rs[i]);
-            if (bw < 0 || sn > bs) {
-                bs = sn;
-                bw = w;
-                bt = t;
+    // ---- peak: (largest S, earliest t) per width (lane i: width i), then the best width ----
+    if (peak && tid < 64) {
+        const int i = tid < a.ne ? tid : -1;
+        double sn = -__builtin_inf();
+        int best = TX_MAX_WIDTHS;
+        int32_t t = 0;
+        if (i >= 0) {
+            t = sh.bT[i];
+            sn = snr_of(T, sh.bS[i], sh.wd[i], sum, inv_d, sh.rs[i]);
+            best = i;
+        }
+#pragma unroll
+        for (int o = TX_MAX_WIDTHS / 2; o > 0; o >>= 1) {     // the smallest width of the largest S/N
+            const double os = __shfl_xor(sn, o);
+            const int ob = __shfl_xor(best, o);
+            const int32_t ot = __shfl_xor(t, o);
+            if (os > sn || (os == sn && ob < best)) {
+                sn = os;
+                best = ob;
+                t = ot;
             }
         }
-        if (bw < 0) {
-            bs = 0.0;
-            bw = a.w_first;
-            bt = 0;
+        if (tid == 0) {
+            to_global(a.snr)[row] = a.ne > 0 ? sn : 0.0;
+            to_global(a.width)[row] = a.ne > 0 ? sh.wd[best] : a.w_first;
+            to_global(a.time)[row] = t;
         }
-        to_global(a.snr)[row] = bs;
-        to_global(a.width)[row] = bw;
-        to_global(a.time)[row] = bt;
     }
 
     // ---- candidates ------------------------------------------------------------------
@@ -440,30 +462,56 @@ __device__ __forceinline__ void row_finish(const BoxcarArgs& a, int row, int nti
         if (tid < a.ne) {
             const int64_t w = sh.wd[tid];
             const double rsw = sh.rs[tid];
+            const auto reaches = [&](int64_t S) { return snr_of(T, S, w, sum, inv_d, rsw) >= a.gamma; };
+            // The least S that reaches gamma: near the exact solution, else by
+            // bisection (the S/N never falls with S).
+            const double x = (a.gamma / (inv_d * rsw) + static_cast<double>(w * sum)) / static_cast<double>(T);
+            const int64_t g = static_cast<int64_t>(__builtin_ceil(fmin(fmax(x, -2147483646.0), 2147483646.0)));
+            const bool r0 = reaches(g - 1), r1 = reaches(g), r2 = reaches(g + 1);
             int64_t lo = INT32_MIN, hi = INT32_MAX;
             int32_t res;
-            if (snr_of(T, lo, w, sum, inv_d, rsw) >= a.gamma) {
+            if (!r0 && r1) {
+                res = static_cast<int32_t>(g);
+            } else if (!r1 && r2) {
+                res = static_cast<int32_t>(g + 1);
+            } else if (reaches(lo)) {
                 res = INT32_MIN;
-            } else if (!(snr_of(T, hi, w, sum, inv_d, rsw) >= a.gamma)) {
+            } else if (!reaches(hi)) {
                 res = INT32_MAX;                          // never reached: window sums are < 2^31 - 1
             } else {
                 while (hi - lo > 1) {                     // snr(lo) < gamma <= snr(hi)
                     const int64_t mid = lo + (hi - lo) / 2;
-                    if (snr_of(T, mid, w, sum, inv_d, rsw) >= a.gamma) hi = mid; else lo = mid;
+                    if (reaches(mid)) hi = mid; else lo = mid;
                 }
                 res = static_cast<int32_t>(hi);
             }
             sh.sthr[tid] = res;
         }
         __syncthreads();
-        for (int tile = 0; tile < ntiles; ++tile) {
-            bool hit = !keep_tmax;
-            if (keep_tmax)
-                for (int i = 0; i < a.ne; ++i) hit = hit || tx_box_tmax[tile * NWT + i] >= max(sh.sthr[i], 0);
-            if (!hit) continue;                           // workgroup-uniform
-            Moments unused;
-            scan_tile<false>(y, T, tile * kBoxTile, L, sh.P, sh.wtot, vec, tid, unused);
-            cand_tile<NWT>(a, sh, row, tile * kBoxTile, sum, inv_d, tid);
+        for (int tb = tlo; tb < thi; tb += kThreads) {    // 256 tiles are looked at together
+            bool hit = tb + tid < thi;
+            if (hit && keep_tmax) {
+                hit = false;
+                for (int i = 0; i < a.ne; ++i) hit = hit || tx_box_tmax[(tb - tlo + tid) * NWT + i] >= max(sh.sthr[i], 0);
+            }
+            const unsigned long long hits = __ballot(hit);
+            if ((tid & 63) == 0) sh.red1[tid >> 6] = hits;
+            __syncthreads();
+            for (int v = 0; v < kWaves; ++v) {
+                const unsigned long long m = sh.red1[v];
+                unsigned long long left =                 // uniform
+                    static_cast<uint32_t>(uniform(static_cast<int>(m))) |
+                    static_cast<unsigned long long>(static_cast<uint32_t>(uniform(static_cast<int>(m >> 32)))) << 32;
+                for (; left; left &= left - 1) {
+                    const int tile = tb + 64 * v + __builtin_ctzll(left);
+                    int tv = tid;                         // opaque, as in row_scan
+                    asm volatile("" : "+v"(tv));
+                    Moments unused;
+                    scan_tile<false>(y, T, tile * kBoxTile, L, sh.P, sh.wtot, vec, tv, unused);
+                    cand_tile<NWT>(a, sh, row, tile, keep_tmax, sum, inv_d, tlo, tv);
+                    __syncthreads();
+                }
+            }
             __syncthreads();
         }
     }
@@ -477,17 +525,19 @@ __device__ __forceinline__ void boxcar_row(const BoxcarArgs& a, int row, BoxShar
     const bool vec = ((reinterpret_cast<uintptr_t>(a.y) + static_cast<uintptr_t>(row) * a.pitch * 4) & 15) == 0;
     const int ntiles = (a.nt + kBoxTile - 1) / kBoxTile;
     const bool keep_tmax = a.tmax_ok != 0;
-    row_setup<NWT>(a, ntiles, keep_tmax, sh, tid);
+    row_setup<NWT>(a, sh, tid);
     row_scan<NWT>(a, 0, ntiles, keep_tmax, y, vec, sh, tid);
-    row_finish<NWT>(a, row, ntiles, keep_tmax, y, vec, sh, tid);
+    row_finish<NWT>(a, row, a.want_peaks != 0, 0, ntiles, keep_tmax, y, vec, sh, tid);
 }
+
+#define TX_BOX_WAVES __attribute__((amdgpu_waves_per_eu(NWT <= 12 ? 7 : NWT <= 16 ? 6 : 5)))
 
 // Single job: one workgroup per row.
 template <int NWT>
 // At least 5 waves per SIMD (at most 102 VGPRs).  When the kernel needed 113
 // VGPRs (4 waves) the cap made it 7% faster despite a 3-dword spill; the
 // current form needs 69 VGPRs with the cap (75 without) and spills nothing.
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void boxcar_kernel(BoxcarArgs a) {
+__global__ __launch_bounds__(kThreads) TX_BOX_WAVES void boxcar_kernel(BoxcarArgs a) {
     __shared__ BoxShared<NWT> sh;
     const int row = static_cast<int>(blockIdx.x);        // grid = rows
     if (row < a.ndm) boxcar_row<NWT>(a, row, sh, static_cast<int>(threadIdx.x));
@@ -505,7 +555,7 @@ __device__ __forceinline__ int find_row_job(const int* __restrict__ prefix, int 
 // Batch form: persistent workgroups taking rows of all jobs (job of a row by
 // prefix sums) from the launch's work counters.
 template <int NWT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void boxcar_batch_kernel(const BoxcarArgs* __restrict__ jobs,
+__global__ __launch_bounds__(kThreads) TX_BOX_WAVES void boxcar_batch_kernel(const BoxcarArgs* __restrict__ jobs,
                                                                 const int* __restrict__ prefix_base,
                                                                 const int* __restrict__ info, uint32_t* queue) {
     __shared__ BoxShared<NWT> sh;
@@ -539,28 +589,43 @@ int boxcar_tmax_bytes(int nwt, int64_t nt) {
     return b <= kTileMaxLds ? static_cast<int>(b) : 0;
 }
 
+struct BoxFns {
+    const void* row;
+    const void* batch;
+};
+
+template <int NWT>
+static BoxFns box_fns() {
+    return {reinterpret_cast<const void*>(&boxcar_kernel<NWT>), reinterpret_cast<const void*>(&boxcar_batch_kernel<NWT>)};
+}
+
+static BoxFns box_fns(int nwt) {
+    switch (nwt) {
+        case 4: return box_fns<4>();
+        case 8: return box_fns<8>();
+        case 10: return box_fns<10>();
+        case 12: return box_fns<12>();
+        case 16: return box_fns<16>();
+        default: return box_fns<32>();
+    }
+}
+
 hipError_t launch_boxcar(const BoxcarArgs& a_in, hipStream_t stream) {
     BoxcarArgs a = a_in;
+    const int nwt = boxcar_nwt(a.ne);
+    const BoxFns fn = box_fns(nwt);
     if (a.want_cands) {
         hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, stream, a.count);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (a.ndm <= 0) return hipSuccess;
-    const int grid = a.ndm;
-    const int nwt = boxcar_nwt(a.ne);
     const int lds = boxcar_tmax_bytes(a.ne, a.nt);
     a.tmax_ok = lds > 0 ? 1 : 0;
     const int prof = prof_begin(TX_KERNEL_BOXCAR, stream);
-    switch (nwt) {
-        case 4: hipLaunchKernelGGL(boxcar_kernel<4>, dim3(grid), dim3(kThreads), lds, stream, a); break;
-        case 8: hipLaunchKernelGGL(boxcar_kernel<8>, dim3(grid), dim3(kThreads), lds, stream, a); break;
-        case 10: hipLaunchKernelGGL(boxcar_kernel<10>, dim3(grid), dim3(kThreads), lds, stream, a); break;
-        case 12: hipLaunchKernelGGL(boxcar_kernel<12>, dim3(grid), dim3(kThreads), lds, stream, a); break;
-        case 16: hipLaunchKernelGGL(boxcar_kernel<16>, dim3(grid), dim3(kThreads), lds, stream, a); break;
-        default: hipLaunchKernelGGL(boxcar_kernel<32>, dim3(grid), dim3(kThreads), lds, stream, a); break;
-    }
-    const hipError_t e = hipGetLastError();
+    void* args[] = {&a};
+    hipError_t e = hipLaunchKernel(fn.row, dim3(a.ndm), dim3(kThreads), args, static_cast<size_t>(lds), stream);
+    if (e == hipSuccess) e = hipGetLastError();
     prof_end(prof, stream);
     return e;
 }
@@ -569,15 +634,7 @@ hipError_t launch_boxcar_batch(int nwt, int lds, const BatchRefs& r, int64_t row
     const BoxcarArgs* jobs = static_cast<const BoxcarArgs*>(r.jobs);
     void* args[] = {&jobs, const_cast<const int**>(&r.prefix), const_cast<const int**>(&r.info),
                     const_cast<uint32_t**>(&r.queue)};
-    const void* fn;
-    switch (boxcar_nwt(nwt)) {
-        case 4: fn = reinterpret_cast<const void*>(&boxcar_batch_kernel<4>); break;
-        case 8: fn = reinterpret_cast<const void*>(&boxcar_batch_kernel<8>); break;
-        case 10: fn = reinterpret_cast<const void*>(&boxcar_batch_kernel<10>); break;
-        case 12: fn = reinterpret_cast<const void*>(&boxcar_batch_kernel<12>); break;
-        case 16: fn = reinterpret_cast<const void*>(&boxcar_batch_kernel<16>); break;
-        default: fn = reinterpret_cast<const void*>(&boxcar_batch_kernel<32>); break;
-    }
+    const void* fn = box_fns(boxcar_nwt(nwt)).batch;
     int grid = resident_grid(fn, lds);
     if (grid <= 0) grid = 256 * 5;
     if (rows > 0 && rows < grid) grid = static_cast<int>(rows);

@@ -682,14 +682,17 @@ static bool mx_fits(const tx_plan_s* p, int64_t nt) {
 // it.  Its matrix products grow with the windows of the plan (DM steps whose
 // delays spread 4 trials over more than 16 samples) and with the trials that
 // fill up the last 16, and few channels per sub-band leave its tables and
-// output pass to be paid by few products.  Measured over 54 plans, blocks of
-// 4096 to 49152 samples (its time of the first stage over the general form's):
-// estimates of 1.1-1.4 0.32-0.73, 1.5-2.0 0.52-0.90, 2.0-3.3 0.36-1.07 (mean
-// 0.80), 3.5-4.7 0.83-1.48 (mean 1.12), above 1.02-2.25.  The plan alone
-// decides, so that scratch sized for a long block serves shorter ones.
+// output pass to be paid by few products.  A plan of few coarse trials leaves
+// CUs idle under the general form, whose tiles are twice as long, and gains
+// longer.  Measured over 80 plans, blocks of 4096 to 49152 samples, its time
+// of the first stage over the general form's: 100 coarse trials or more, estimates of
+// 1.2-1.6 0.45-0.78, 1.6-2.0 0.52-0.94, 2.0-2.35 0.62-1.00, 2.35-2.9 0.96-1.12,
+// above 1.03-2.3; fewer trials, 1.3-3.3 0.32-0.96 (one of 20 1.07), above
+// 0.83-2.25 (mean 1.3).  The plan alone decides, so that scratch sized for a
+// long block serves shorter ones.
 static bool mx_pays(const tx_plan_s* p) {
     const double padded = static_cast<double>((p->ngroups + 15) / 16 * 16) / p->ngroups;
-    return p->mx.windows * padded * (1.0 + 5.0 / p->m) < 3.4;
+    return (p->mx.windows + 10.0 / p->m) * padded < (p->ngroups < 100 ? 3.3 : 2.35);
 }
 
 bool default_stage1(const Tiles& t) { return t.s1 < 0 || t.s1 >= kNS1; }
