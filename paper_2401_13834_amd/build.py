@@ -23,7 +23,7 @@ ARCH = "gfx950"
 
 HIP_SOURCES = ["tx_kernels_dedisp.hip", "tx_kernels_boxcar.hip", "tx_kernels_transpose.hip",
                "tx_kernels_downsample.hip", "tx_kernels_cluster.hip", "tx_kernels_stats.hip", "tx_kernels_norm.hip"]
-HOST_SOURCES = ["tx_plan.cpp", "tx_api.cpp", "tx_profile.cpp", "tx_stream.cpp", "tx_batch.cpp", "tx_autotune.cpp",
+HOST_SOURCES = ["tx_plan.cpp", "tx_api.cpp", "tx_scratch.cpp", "tx_profile.cpp", "tx_stream.cpp", "tx_batch.cpp", "tx_autotune.cpp",
                 "tx_ranges.cpp", "tx_cluster.cpp", "tx_mask.cpp", "tx_norm.cpp"]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-ffp-contract=off", "-Wall", "-Wno-unused-result"]

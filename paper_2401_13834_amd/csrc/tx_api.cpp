@@ -277,6 +277,7 @@ tx_status tx_pool_trim(void) {
     hipMemPool_t pool;
     hipError_t e = hipDeviceSynchronize();
     if (e == hipSuccess) e = hipDeviceGetDefaultMemPool(&pool, dev);
+    if (e == hipSuccess) tx::scratch_trim(dev);
     if (e == hipSuccess) e = hipMemPoolTrimTo(pool, 0);
     return from_hip(e);
 }
@@ -347,11 +348,11 @@ tx_status tx_dedisperse(tx_plan_t p, const uint8_t* d_in, int64_t in_pitch, int6
     if (st != TX_OK) return st;
     const tx::DedispGeom geo = tx::dedisp_geometry(p, nt, current_tiles(p));
     if (!geo.ok) return TX_ENOTSUP;
-    void* ws = nullptr;
-    hipError_t e = hipMallocAsync(&ws, static_cast<size_t>(geo.ws_bytes), stream);
+    tx::Scratch ws;
+    hipError_t e = tx::scratch_get(static_cast<size_t>(geo.ws_bytes), stream, &ws);
     if (e != hipSuccess) return from_hip(e);
-    e = tx::launch_dedisperse(p, geo, d_in, in_pitch, nt, d_out, out_pitch, static_cast<uint16_t*>(ws), stream);
-    hipError_t f = hipFreeAsync(ws, stream);
+    e = tx::launch_dedisperse(p, geo, d_in, in_pitch, nt, d_out, out_pitch, static_cast<uint16_t*>(ws.p), stream);
+    hipError_t f = tx::scratch_put(&ws, stream);
     if (e != hipSuccess) return from_hip(e);
     return from_hip(f);
 }

@@ -45,12 +45,12 @@ tx_status tx_cluster(tx_plan_t p, const tx_cand* d_cands, int64_t n, double radi
         lohi[d] = lo;
         lohi[ndm + d] = hi;
     }
-    void* buf = nullptr;
+    tx::Scratch buf;
     const size_t xb = sizeof(double) * ndm, lb = sizeof(int32_t) * 2 * ndm;
-    hipError_t e = hipMallocAsync(&buf, xb + lb, stream);
+    hipError_t e = tx::scratch_get(xb + lb, stream, &buf);
     if (e != hipSuccess) return tx::status_of(e);
-    double* d_x = static_cast<double*>(buf);
-    int32_t* d_lohi = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(buf) + xb);
+    double* d_x = static_cast<double*>(buf.p);
+    int32_t* d_lohi = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(buf.p) + xb);
     e = hipMemcpyAsync(d_x, x.data(), xb, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(d_lohi, lohi.data(), lb, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess)
@@ -58,7 +58,7 @@ tx_status tx_cluster(tx_plan_t p, const tx_cand* d_cands, int64_t n, double radi
                                d_nclusters, stream);
     // The host tables must outlive the copies.
     const hipError_t s = hipStreamSynchronize(stream);
-    const hipError_t f = hipFreeAsync(buf, stream);
+    const hipError_t f = tx::scratch_put(&buf, stream);
     if (e == hipSuccess) e = s;
     if (e == hipSuccess) e = f;
     return tx::status_of(e);

@@ -364,6 +364,16 @@ int boxcar_nwt(int n);
 tx_status status_of(hipError_t e);
 // Keep freed stream-ordered scratch in the device's pool (idempotent per device).
 tx_status retain_pool(int dev);
+// Scratch of one call's kernels on `stream` (256-byte aligned): a buffer kept
+// from an earlier call where one fits, else the device's pool (after
+// retain_pool).  scratch_put, after the last kernel, gives it back.
+struct Scratch {
+    void* p = nullptr;
+    void* kept = nullptr;
+};
+hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out);
+hipError_t scratch_put(Scratch* s, hipStream_t stream);
+void scratch_trim(int dev);             // frees the kept buffers (device idle)
 tx::Tiles plan_tiles(const tx_plan_s* p);
 
 // Host plan construction (tx_plan.cpp).

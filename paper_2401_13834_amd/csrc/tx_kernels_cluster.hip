@@ -260,10 +260,10 @@ hipError_t launch_cluster(const tx_cand* d_in, int64_t n, int32_t ndm, const dou
         return hipGetLastError();
     }
     const ClusterScratch L = cluster_layout(n, ndm);
-    void* ws = nullptr;
-    hipError_t e = hipMallocAsync(&ws, L.total, st);
+    Scratch ws;
+    hipError_t e = scratch_get(L.total, st, &ws);
     if (e != hipSuccess) return e;
-    uint8_t* w = static_cast<uint8_t*>(ws);
+    uint8_t* w = static_cast<uint8_t*>(ws.p);
     auto at = [&](size_t off) { return static_cast<void*>(w + off); };
     uint64_t* keys = static_cast<uint64_t*>(at(L.keys));
     uint64_t* keys2 = static_cast<uint64_t*>(at(L.keys2));
@@ -306,7 +306,7 @@ hipError_t launch_cluster(const tx_cand* d_in, int64_t n, int32_t ndm, const dou
         hipLaunchKernelGGL(count_kernel, dim3(1), dim3(64), 0, st, n32, cid, is_root, d_nclusters);
         e = hipGetLastError();
     }
-    const hipError_t f = hipFreeAsync(ws, st);
+    const hipError_t f = scratch_put(&ws, st);
     return e != hipSuccess ? e : f;
 }
 

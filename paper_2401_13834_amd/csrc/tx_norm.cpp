@@ -112,12 +112,12 @@ tx_status tx_dedisperse_norm(tx_plan_t p, const uint8_t* d_in, int64_t in_pitch,
     if (st != TX_OK) return st;
     const tx::NormGeom g = tx::norm_geometry(p, nt);
     if (!g.ok) return TX_ENOTSUP;
-    void* ws = nullptr;
-    hipError_t e = hipMallocAsync(&ws, static_cast<size_t>(g.ws_bytes), stream);
+    tx::Scratch ws;
+    hipError_t e = tx::scratch_get(static_cast<size_t>(g.ws_bytes), stream, &ws);
     if (e != hipSuccess) return tx::status_of(e);
     e = tx::launch_dedisperse_norm(p, g, d_in, in_pitch, nt, d_scale, d_offset, d_out, out_pitch,
-                                   static_cast<float*>(ws), stream);
-    const hipError_t f = hipFreeAsync(ws, stream);
+                                   static_cast<float*>(ws.p), stream);
+    const hipError_t f = tx::scratch_put(&ws, stream);
     if (e != hipSuccess) return tx::status_of(e);
     return tx::status_of(f);
 }

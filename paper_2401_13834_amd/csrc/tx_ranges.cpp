@@ -91,7 +91,7 @@ tx_status tx_ranges_dedisperse(tx_ranges_t r, const uint8_t* d_in, int64_t in_pi
     std::vector<int32_t> ks;
     for (int32_t k : r->factors)
         if (k > 1 && std::find(ks.begin(), ks.end(), k) == ks.end()) ks.push_back(k);
-    std::vector<void*> bufs(ks.size(), nullptr);
+    std::vector<tx::Scratch> bufs(ks.size());
     std::vector<int64_t> pitches(ks.size(), 0);
     hipError_t e = hipSuccess;
     for (size_t b = 0; b < ks.size() && e == hipSuccess; ++b) {
@@ -99,9 +99,9 @@ tx_status tx_ranges_dedisperse(tx_ranges_t r, const uint8_t* d_in, int64_t in_pi
         for (size_t i = 0; i < n; ++i)
             if (r->factors[i] == ks[b]) len = std::max(len, nt / ks[b] + r->plans[i]->overlap);
         pitches[b] = (len + 255) / 256 * 256;
-        e = hipMallocAsync(&bufs[b], static_cast<size_t>(pitches[b]) * r->nchan, stream);
+        e = tx::scratch_get(static_cast<size_t>(pitches[b]) * r->nchan, stream, &bufs[b]);
         if (e == hipSuccess)
-            e = tx::launch_downsample(d_in, in_pitch, r->nchan, len, ks[b], static_cast<uint8_t*>(bufs[b]),
+            e = tx::launch_downsample(d_in, in_pitch, r->nchan, len, ks[b], static_cast<uint8_t*>(bufs[b].p),
                                       pitches[b], stream);
     }
     // Each range: its own plan on its (downsampled) copy.
@@ -114,7 +114,7 @@ tx_status tx_ranges_dedisperse(tx_ranges_t r, const uint8_t* d_in, int64_t in_pi
         int64_t pitch = in_pitch;
         if (k > 1) {
             const size_t b = static_cast<size_t>(std::find(ks.begin(), ks.end(), k) - ks.begin());
-            in = static_cast<const uint8_t*>(bufs[b]);
+            in = static_cast<const uint8_t*>(bufs[b].p);
             pitch = pitches[b];
         }
         const tx::DedispGeom geo = tx::dedisp_geometry(p, nt_r, tx::plan_tiles(p));
@@ -122,16 +122,15 @@ tx_status tx_ranges_dedisperse(tx_ranges_t r, const uint8_t* d_in, int64_t in_pi
             st = TX_ENOTSUP;
             break;
         }
-        void* ws = nullptr;
-        e = hipMallocAsync(&ws, static_cast<size_t>(geo.ws_bytes), stream);
+        tx::Scratch ws;
+        e = tx::scratch_get(static_cast<size_t>(geo.ws_bytes), stream, &ws);
         if (e != hipSuccess) break;
-        e = tx::launch_dedisperse(p, geo, in, pitch, nt_r, d_outs[i], out_pitches[i], static_cast<uint16_t*>(ws),
+        e = tx::launch_dedisperse(p, geo, in, pitch, nt_r, d_outs[i], out_pitches[i], static_cast<uint16_t*>(ws.p),
                                   stream);
-        const hipError_t f = hipFreeAsync(ws, stream);
+        const hipError_t f = tx::scratch_put(&ws, stream);
         if (e == hipSuccess) e = f;
     }
-    for (void* b : bufs)
-        if (b) (void)hipFreeAsync(b, stream);
+    for (tx::Scratch& b : bufs) (void)tx::scratch_put(&b, stream);
     if (st != TX_OK) return st;
     return tx::status_of(e);
 }

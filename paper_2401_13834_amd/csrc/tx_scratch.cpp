@@ -1,0 +1,138 @@
+// Scratch of one call's kernels, kept between calls.
+//
+// hipMallocAsync and hipFreeAsync cost a call 14 us on the host (a dedispersion
+// of 102 trials x 12464 samples 27.6, now 13.4), and 40 to
+// 100 us each when a call makes several of different sizes (the three ranges of a
+// 128-channel block: 435 us a call, 40 us with these buffers), more than the
+// kernels of a small block take.  Here a buffer of up to kMaxBuf bytes stays
+// allocated after the call and is taken again by a later one: by a call on the
+// same stream, which its kernels follow, or by any once the event recorded
+// behind the last user's kernels has completed.  Larger buffers, captures and calls that
+// find neither a free buffer nor room for another use the stream-ordered pool
+// as before.  Per device at most kMaxBufs buffers and kMaxBytes bytes are
+// kept; tx_pool_trim gives them back.
+#include <mutex>
+
+#include "tx_internal.h"
+
+namespace tx {
+namespace {
+
+constexpr size_t kMinBuf = size_t(4) << 20;
+constexpr size_t kMaxBuf = size_t(64) << 20;
+constexpr size_t kMaxBytes = size_t(512) << 20;
+constexpr int kMaxBufs = 16;
+
+struct Buf {
+    void* p = nullptr;
+    size_t bytes = 0;
+    hipEvent_t done = nullptr;
+    hipStream_t last = nullptr;
+    bool used = false;      // `done` has been recorded
+    bool busy = false;      // a call holds it
+};
+
+struct DevBufs {
+    Buf bufs[kMaxBufs];     // p null: no buffer
+    size_t bytes = 0;
+};
+
+constexpr int kMaxDevices = 64;
+std::mutex g_mu;
+DevBufs g_dev[kMaxDevices];
+
+// Calls that a capture elsewhere in the process forbids are allowed for the
+// scope: none of them touches a capturing stream.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+void free_buf(Buf* b) {
+    if (b->p) (void)hipFree(b->p);
+    if (b->done) (void)hipEventDestroy(b->done);
+    *b = Buf{};
+}
+
+// A kept buffer of at least `bytes` for `stream`, or null.  Called with g_mu held.
+Buf* take(DevBufs& d, size_t bytes, hipStream_t stream) {
+    Buf* best = nullptr;
+    Buf* empty = nullptr;
+    for (Buf& b : d.bufs) {                          // the smallest that is ready
+        if (!b.p) {
+            empty = &b;
+            continue;
+        }
+        if (b.busy || b.bytes < bytes || (best && b.bytes >= best->bytes)) continue;
+        if (b.used && b.last != stream && hipEventQuery(b.done) != hipSuccess) continue;
+        best = &b;
+    }
+    // (The handle may be another stream's by now, so also the same handle
+    // waits for the event; on the stream that recorded it that is nothing.)
+    if (best && best->used && best->last == stream && hipStreamWaitEvent(stream, best->done, 0) != hipSuccess)
+        best = nullptr;
+    if (!best) {
+        size_t size = kMinBuf;
+        while (size < bytes) size *= 2;
+        if (!empty || d.bytes + size > kMaxBytes) return nullptr;
+        if (hipMalloc(&empty->p, size) != hipSuccess ||
+            hipEventCreateWithFlags(&empty->done, hipEventDisableTiming) != hipSuccess) {
+            free_buf(empty);
+            return nullptr;
+        }
+        empty->bytes = size;
+        d.bytes += size;
+        best = empty;
+    }
+    best->busy = true;
+    return best;
+}
+
+}  // namespace
+
+hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out) {
+    *out = Scratch{};
+    int dev = -1;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+    if (bytes <= kMaxBuf && hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+        hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) {
+        RelaxedCapture relaxed;
+        std::lock_guard<std::mutex> lock(g_mu);
+        if (Buf* b = take(g_dev[dev], bytes, stream)) {
+            out->p = b->p;
+            out->kept = b;
+        }
+    }
+    (void)hipGetLastError();                         // (an event that has not completed is no error)
+    if (out->p) return hipSuccess;
+    return hipMallocAsync(&out->p, bytes > 0 ? bytes : 1, stream);
+}
+
+hipError_t scratch_put(Scratch* s, hipStream_t stream) {
+    if (!s->p) return hipSuccess;
+    Buf* b = static_cast<Buf*>(s->kept);
+    void* p = s->p;
+    *s = Scratch{};
+    if (!b) return hipFreeAsync(p, stream);
+    hipError_t e = hipEventRecord(b->done, stream);
+    if (e != hipSuccess) e = hipStreamSynchronize(stream);      // nothing to wait for later then
+    std::lock_guard<std::mutex> lock(g_mu);
+    b->used = true;
+    b->last = stream;
+    b->busy = false;
+    return e;
+}
+
+void scratch_trim(int dev) {
+    if (dev < 0 || dev >= kMaxDevices) return;
+    std::lock_guard<std::mutex> lock(g_mu);
+    DevBufs& d = g_dev[dev];
+    for (Buf& b : d.bufs) {
+        if (!b.p || b.busy) continue;
+        d.bytes -= b.bytes;
+        free_buf(&b);
+    }
+}
+
+}  // namespace tx
