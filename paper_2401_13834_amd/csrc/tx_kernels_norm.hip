@@ -329,9 +329,10 @@ template <int NWT>
 struct NormBoxShared {
     double wsum[kWaves];
     double red1[kWaves], red2[kWaves];
-    double wm[kWaves][NWT];              // per wavefront: largest sum per width in this tile,
-    double wS[kWaves][NWT];              // the largest so far, and
-    int32_t wT[kWaves][NWT];             // its earliest start
+    __align__(16) double wS[NWT][kWaves];    // the tile's largest sum per width and wavefront, and where
+    __align__(16) int32_t wT[NWT][kWaves];   // it is the row's new best, its earliest start
+    double bS[NWT];                      // per width: the row's largest sum so far and
+    int32_t bT[NWT];                     // its earliest start
     double sthr[NWT];                    // least sum reaching gamma per width (NaN: none)
     int32_t wd[NWT];
     double rs[NWT];
@@ -470,59 +471,75 @@ __device__ __forceinline__ void norm_scan_tile(const TX_GLOBAL float* __restrict
     __syncthreads();
 }
 
-// Per-width largest sums of one tile (each wavefront's in sh.wm) and the
-// wavefront bests.  TAIL: some windows reach past the row end (they count as
-// -inf).
+// Per-width largest sums of one tile (into `tmax` where there is one) and the
+// row's bests.  First every wavefront's largest sums of all widths; then, where
+// the tile beats the row's best sum of a width (a few tiles per row), the
+// wavefronts that hold that sum look up its earliest start.  Comparing with
+// the whole row's best, and not each wavefront with its own, leaves a quarter
+// of the lookups.  4096 rows of 65536 samples, 8 widths: 867 us with lookups
+// per wavefront and unrolled widths, 701 so; 168 rows of 5003 samples 35 and 23.
+// TAIL: some windows reach past the row end (they count as -inf).
 template <int NWT, bool TAIL>
-__device__ __forceinline__ void norm_peak_tile(NormBoxShared<NWT>& sh, int T, int t0, int tid) {
-    const int wave = tid >> 6;
+__device__ __forceinline__ void norm_peak_tile(NormBoxShared<NWT>& sh, int T, int t0, int tid, double* tmax) {
+    const int wave = tid >> 6, lane = tid & 63;
     double Pt[kNormBoxPer];
 #pragma unroll
     for (int j = 0; j < kNormBoxPer; ++j) Pt[j] = tx_nbox_dyn[tid + 256 * j];
-    double tm[NWT];
-#pragma unroll
-    for (int i = 0; i < NWT; ++i) {
-        const int w = sh.wd[i];
-        const double* p = tx_nbox_dyn + tid + w;
-        double m = -__builtin_inf();
+#pragma unroll 1
+    for (int i = 0; i < NWT; i += 2) {
+        const int w0 = sh.wd[i], w1 = sh.wd[i + 1];
+        const double* p0 = tx_nbox_dyn + tid + w0;
+        const double* p1 = tx_nbox_dyn + tid + w1;
+        double m0 = -__builtin_inf(), m1 = -__builtin_inf();
 #pragma unroll
         for (int j = 0; j < kNormBoxPer; ++j) {
-            double S = p[256 * j] - Pt[j];
-            if (TAIL) S = t0 + tid + 256 * j + w <= T ? S : -__builtin_inf();
-            m = __builtin_fmax(m, S);
-        }
-        tm[i] = m;
-        // Keep each width's LDS reads next to their arithmetic.
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    // Wavefront maxima (independent reductions, interleaved), left in LDS
-    // for the rolled loop below to read by width.
-    double wm[NWT];
-#pragma unroll
-    for (int i = 0; i < NWT; ++i) wm[i] = wave_max_d(tm[i]);
-    if ((tid & 63) == 0) {
-#pragma unroll
-        for (int i = 0; i < NWT; ++i) sh.wm[wave][i] = wm[i];
-    }
-#pragma unroll 1
-    for (int ii = 0; ii < NWT; ++ii) {
-        const double m = sh.wm[wave][ii];
-        if (m > sh.wS[wave][ii]) {                      // wavefront-uniform, a few tiles per row
-            const int w = sh.wd[ii];
-            int32_t first = INT32_MAX;
-#pragma unroll 1
-            for (int j = kNormBoxPer - 1; j >= 0; --j) {   // rolled: this path is rare
-                const int e = tid + 256 * j;
-                const int t = t0 + e;
-                const double S = tx_nbox_dyn[e + w] - tx_nbox_dyn[e];
-                first = ((!TAIL || t + w <= T) && S == m) ? t : first;
+            const int t = t0 + tid + 256 * j;
+            double S0 = p0[256 * j] - Pt[j], S1 = p1[256 * j] - Pt[j];
+            if (TAIL) {
+                S0 = t + w0 <= T ? S0 : -__builtin_inf();
+                S1 = t + w1 <= T ? S1 : -__builtin_inf();
             }
-            const int32_t ft = wave_min_i32_n(first);
-            if ((tid & 63) == 0) {
-                sh.wS[wave][ii] = m;
-                sh.wT[wave][ii] = ft;
-            }
+            m0 = __builtin_fmax(m0, S0);
+            m1 = __builtin_fmax(m1, S1);
         }
+        m0 = wave_max_d(m0);
+        m1 = wave_max_d(m1);
+        if (lane < 2) sh.wS[i + lane][wave] = lane == 0 ? m0 : m1;
+    }
+    __syncthreads();
+    // Lane i: width i.
+    double M = -__builtin_inf();
+    bool look = false;
+    if (lane < NWT) {
+        M = __builtin_fmax(__builtin_fmax(sh.wS[lane][0], sh.wS[lane][1]),
+                           __builtin_fmax(sh.wS[lane][2], sh.wS[lane][3]));
+        if (tmax && wave == 0) tmax[lane] = M;
+        look = M > sh.bS[lane];
+    }
+    if (__ballot(look) == 0) return;                          // the same in every wavefront
+    for (unsigned long long left = __ballot(look && sh.wS[lane < NWT ? lane : 0][wave] == M); left; left &= left - 1) {
+        const int i = __builtin_ctzll(left);
+        const double m = sh.wS[i][wave];
+        const int w = sh.wd[i];
+        const double* p = tx_nbox_dyn + tid + w;
+        int32_t first = INT32_MAX;
+#pragma unroll
+        for (int j = kNormBoxPer - 1; j >= 0; --j) {
+            const int t = t0 + tid + 256 * j;
+            const double S = p[256 * j] - Pt[j];
+            first = ((!TAIL || t + w <= T) && S == m) ? t : first;
+        }
+        const int32_t ft = wave_min_i32_n(first);
+        if (lane == 0) sh.wT[i][wave] = ft;
+    }
+    __syncthreads();
+    if (wave == 0 && look) {
+        int32_t t = INT32_MAX;
+#pragma unroll
+        for (int v = 0; v < kWaves; ++v)
+            if (sh.wS[lane][v] == M) t = min(t, sh.wT[lane][v]);
+        sh.bS[lane] = M;
+        sh.bT[lane] = t;
     }
 }
 
@@ -586,13 +603,8 @@ __global__ __launch_bounds__(kThreads) void boxcar_norm_kernel(BoxcarNormArgs a)
             }
         sh.wd[tid] = w;
         sh.rs[tid] = r;
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int i = 0; i < NWT; ++i) {
-            sh.wS[wave][i] = -__builtin_inf();
-            sh.wT[wave][i] = 0;
-        }
+        sh.bS[tid] = -__builtin_inf();
+        sh.bT[tid] = 0;
     }
     // (the first tile's barriers order these writes before their reads)
 
@@ -606,15 +618,11 @@ __global__ __launch_bounds__(kThreads) void boxcar_norm_kernel(BoxcarNormArgs a)
         asm volatile("" : "+v"(tv));
         norm_scan_tile<true, NWT>(y, T, t0, L, vec, sh, tv, m1, m2);
         if (a.ne > 0) {
-            if (t0 + kNormBoxTile + a.wmax > T) norm_peak_tile<NWT, true>(sh, T, t0, tv);
-            else norm_peak_tile<NWT, false>(sh, T, t0, tv);
+            double* tm = keep_tmax ? tmax + tile * NWT : nullptr;
+            if (t0 + kNormBoxTile + a.wmax > T) norm_peak_tile<NWT, true>(sh, T, t0, tv, tm);
+            else norm_peak_tile<NWT, false>(sh, T, t0, tv, tm);
         }
         __syncthreads();
-        // The workgroup's largest sum per width of this tile (the next tile's
-        // barriers order this before sh.wm is written again).
-        if (keep_tmax && tid < NWT)
-            tmax[tile * NWT + tid] = __builtin_fmax(__builtin_fmax(sh.wm[0][tid], sh.wm[1][tid]),
-                                                    __builtin_fmax(sh.wm[2][tid], sh.wm[3][tid]));
     }
 
     // Statistics.
@@ -651,7 +659,7 @@ __global__ __launch_bounds__(kThreads) void boxcar_norm_kernel(BoxcarNormArgs a)
     }
     const double mean = sh.mean, inv = sh.inv;
 
-    // The row's peak: per width the largest sum over the wavefronts (earliest
+    // The row's peak: per width the largest sum (earliest
     // start on ties) and its S/N; the largest S/N over widths, ties to the
     // smaller width.
     if (tid == 0 && a.want_peaks) {
@@ -659,13 +667,8 @@ __global__ __launch_bounds__(kThreads) void boxcar_norm_kernel(BoxcarNormArgs a)
         int bw = -1;
         int64_t btm = 0;
         for (int i = 0; i < a.ne; ++i) {
-            double S = sh.wS[0][i];
-            int32_t t = sh.wT[0][i];
-            for (int w2 = 1; w2 < kWaves; ++w2)
-                if (sh.wS[w2][i] > S || (sh.wS[w2][i] == S && sh.wT[w2][i] < t)) {
-                    S = sh.wS[w2][i];
-                    t = sh.wT[w2][i];
-                }
+            const double S = sh.bS[i];
+            const int32_t t = sh.bT[i];
             if (S == -__builtin_inf()) continue;
             const double s = snr_f(S, sh.wd[i], mean, inv, sh.rs[i]);
             if (bw < 0 || s > best) {
