@@ -30,6 +30,8 @@ namespace tx {
 // read every tile again for candidates.
 constexpr int kTileMaxLds = 16 * 1024;
 
+constexpr int kSplitGroups = 6 * 256;   // workgroups that a split aims at
+
 template <int NWT>
 struct BoxShared {
     __align__(16) uint32_t P[kBoxTile + TX_MAX_WIDTH + 16];
@@ -194,7 +196,7 @@ __device__ __forceinline__ void scan_tile(const TX_GLOBAL int32_t* __restrict__ 
 // lookups, and each costs about as much as a width's sums.  The widths are a
 // rolled loop, two a turn: a row's code is a third of the unrolled one's.
 // 4096 rows of 65536 samples, 10 widths: 521 us with lookups per wavefront and
-// unrolled widths, 365 so (1.07 GB: 2.9 TB/s); 96 rows of 1000003 samples 1340 and 1100.
+// unrolled widths, 365 so (1.07 GB: 2.9 TB/s); 96 rows of 1000003 samples, unsplit, 1340 and 950.
 template <int NWT, bool TAIL>
 __device__ __forceinline__ void peak_tile(const BoxcarArgs& a, BoxShared<NWT>& sh, int tile, int t0, int tid,
                                           bool keep_tmax) {
@@ -543,6 +545,103 @@ __global__ __launch_bounds__(kThreads) TX_BOX_WAVES void boxcar_kernel(BoxcarArg
     if (row < a.ndm) boxcar_row<NWT>(a, row, sh, static_cast<int>(threadIdx.x));
 }
 
+// Few rows: each row's tiles are split over `parts` workgroups, in two
+// launches.  The first leaves every part's moments, per-width best and
+// per-(tile, width) maxima in `ws`; in the second every part of a row puts
+// the row together from them, the first part writes its peak and each lists
+// the candidates of its own tiles.
+struct BoxSplit {
+    uint8_t* ws;
+    int32_t parts;          // per row, at most 64
+    int32_t tpp;            // tiles per part
+};
+
+template <int NWT>
+struct BoxPart {
+    unsigned long long s1, s2;
+    int32_t bad, pad;
+    int32_t S[NWT], t[NWT];
+};
+
+template <int NWT>
+__global__ __launch_bounds__(kThreads) TX_BOX_WAVES void boxcar_scan_kernel(BoxcarArgs a, BoxSplit sp) {
+    __shared__ BoxShared<NWT> sh;
+    const int tid = static_cast<int>(threadIdx.x);
+    const int row = static_cast<int>(blockIdx.x) / sp.parts;
+    const int part = static_cast<int>(blockIdx.x) % sp.parts;
+    if (row >= a.ndm) return;
+    if (blockIdx.x == 0 && tid == 0 && a.want_cands) *a.count = 0ull;      // (the next launch counts)
+    const TX_GLOBAL int32_t* __restrict__ y = to_global(a.y) + static_cast<size_t>(row) * a.pitch;
+    const bool vec = ((reinterpret_cast<uintptr_t>(a.y) + static_cast<uintptr_t>(row) * a.pitch * 4) & 15) == 0;
+    const int ntiles = (a.nt + kBoxTile - 1) / kBoxTile;
+    const int tlo = part * sp.tpp, thi = min(tlo + sp.tpp, ntiles);
+    row_setup<NWT>(a, sh, tid);
+    row_scan<NWT>(a, tlo, thi, true, y, vec, sh, tid);
+    BoxPart<NWT>* parts = reinterpret_cast<BoxPart<NWT>*>(sp.ws);
+    BoxPart<NWT>* p = parts + blockIdx.x;
+    if (tid == 0) {
+        unsigned long long s1 = 0, s2 = 0;
+        int bad = 0;
+        for (int v = 0; v < kWaves; ++v) {
+            s1 += sh.red1[v];
+            s2 += sh.red2[v];
+            bad |= sh.redbad[v];
+        }
+        p->s1 = s1;
+        p->s2 = s2;
+        p->bad = bad;
+    }
+    if (tid < NWT) {
+        p->S[tid] = sh.bS[tid];
+        p->t[tid] = sh.bT[tid];
+    }
+    int32_t* tm = reinterpret_cast<int32_t*>(parts + static_cast<size_t>(a.ndm) * sp.parts) +
+                  static_cast<size_t>(blockIdx.x) * sp.tpp * NWT;
+    for (int k = tid; k < (thi - tlo) * NWT; k += kThreads) tm[k] = tx_box_tmax[k];
+}
+
+template <int NWT>
+__global__ __launch_bounds__(kThreads) TX_BOX_WAVES void boxcar_finish_kernel(BoxcarArgs a, BoxSplit sp) {
+    __shared__ BoxShared<NWT> sh;
+    const int tid = static_cast<int>(threadIdx.x);
+    const int lane = tid & 63, wave = tid >> 6;
+    const int row = static_cast<int>(blockIdx.x) / sp.parts;
+    const int part = static_cast<int>(blockIdx.x) % sp.parts;
+    if (row >= a.ndm) return;
+    const TX_GLOBAL int32_t* __restrict__ y = to_global(a.y) + static_cast<size_t>(row) * a.pitch;
+    const bool vec = ((reinterpret_cast<uintptr_t>(a.y) + static_cast<uintptr_t>(row) * a.pitch * 4) & 15) == 0;
+    const int ntiles = (a.nt + kBoxTile - 1) / kBoxTile;
+    const int tlo = part * sp.tpp, thi = min(tlo + sp.tpp, ntiles);
+    const BoxPart<NWT>* parts = reinterpret_cast<const BoxPart<NWT>*>(sp.ws);
+    row_setup<NWT>(a, sh, tid);
+    const int32_t* tm = reinterpret_cast<const int32_t*>(parts + static_cast<size_t>(a.ndm) * sp.parts) +
+                        static_cast<size_t>(blockIdx.x) * sp.tpp * NWT;
+    for (int k = tid; k < (thi - tlo) * NWT; k += kThreads) tx_box_tmax[k] = tm[k];
+    const BoxPart<NWT>* p = parts + static_cast<size_t>(row) * sp.parts + (lane < sp.parts ? lane : 0);   // lane: part
+    const bool own = lane < sp.parts;
+    if (wave == 0) {
+        const unsigned long long s1 = wave_sum(own ? p->s1 : 0ull);
+        const unsigned long long s2 = wave_sum(own ? p->s2 : 0ull);
+        const int bad = __any(own && p->bad != 0) ? 1 : 0;
+        if (lane < kWaves) {
+            sh.red1[lane] = lane == 0 ? s1 : 0ull;
+            sh.red2[lane] = lane == 0 ? s2 : 0ull;
+            sh.redbad[lane] = bad;
+        }
+    }
+    for (int i = wave; i < NWT; i += kWaves) {
+        const int32_t S = own ? p->S[i] : INT32_MIN;
+        const int32_t m = wave_max_i32(S);
+        const int32_t t = wave_min_i32(own && S == m ? p->t[i] : INT32_MAX);
+        if (lane == 0) {
+            sh.bS[i] = m;
+            sh.bT[i] = t;
+        }
+    }
+    __syncthreads();
+    row_finish<NWT>(a, row, a.want_peaks != 0 && part == 0, tlo, thi, true, y, vec, sh, tid);
+}
+
 __device__ __forceinline__ int find_row_job(const int* __restrict__ prefix, int njobs, int v) {
     int lo = 0, hi = njobs;
     while (hi - lo > 1) {
@@ -591,12 +690,17 @@ int boxcar_tmax_bytes(int nwt, int64_t nt) {
 
 struct BoxFns {
     const void* row;
+    const void* scan;
+    const void* finish;
     const void* batch;
+    int part_bytes;
 };
 
 template <int NWT>
 static BoxFns box_fns() {
-    return {reinterpret_cast<const void*>(&boxcar_kernel<NWT>), reinterpret_cast<const void*>(&boxcar_batch_kernel<NWT>)};
+    return {reinterpret_cast<const void*>(&boxcar_kernel<NWT>), reinterpret_cast<const void*>(&boxcar_scan_kernel<NWT>),
+            reinterpret_cast<const void*>(&boxcar_finish_kernel<NWT>),
+            reinterpret_cast<const void*>(&boxcar_batch_kernel<NWT>), static_cast<int>(sizeof(BoxPart<NWT>))};
 }
 
 static BoxFns box_fns(int nwt) {
@@ -610,10 +714,57 @@ static BoxFns box_fns(int nwt) {
     }
 }
 
+// Split of a row's tiles over workgroups (parts 1: none): as far as 6
+// workgroups per CU, where they still run side by side at little cost, but
+// parts of at least 1 + rows / 128 tiles, and only rows of 3 such parts: the
+// second launch costs about 10 us, a tile 4 us on an idle CU and more on a
+// full one.  Measured unsplit and split (10 widths, candidates in
+// every row): 96 x 1000003 samples 950 and 154 us, 128 x 28749 60 and 41,
+// 256 x 61517 97 and 67, 512 x 61517 114 and 87, 512 x 245837 400 and 253;
+// without the limits 512 x 12365 46 and 63, 768 x 61517 130 and 132, 1024 x 61517
+// 149 and 180.
+static BoxSplit box_split(int rows, int ntiles, int nwt) {
+    const int unit = 1 + rows / 128;
+    const int parts = ntiles >= 3 * unit ? std::min({ntiles / unit, 64, kSplitGroups / rows}) : 1;
+    if (parts < 2) return {nullptr, 1, ntiles};
+    const int tpp = (ntiles + parts - 1) / parts;
+    if (tpp * nwt * 4 > kTileMaxLds) return {nullptr, 1, ntiles};
+    return {nullptr, (ntiles + tpp - 1) / tpp, tpp};
+}
+
 hipError_t launch_boxcar(const BoxcarArgs& a_in, hipStream_t stream) {
     BoxcarArgs a = a_in;
     const int nwt = boxcar_nwt(a.ne);
     const BoxFns fn = box_fns(nwt);
+    // A split needs scratch; without (or in a capture, which stays one
+    // kernel) the rows are not split.
+    BoxSplit sp{nullptr, 1, 0};
+    Scratch ws;
+    if (a.ndm > 0) sp = box_split(a.ndm, (a.nt + kBoxTile - 1) / kBoxTile, nwt);
+    if (sp.parts > 1) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+        int dev = -1;
+        const int64_t n = static_cast<int64_t>(a.ndm) * sp.parts;
+        if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+            hipGetDevice(&dev) != hipSuccess || retain_pool(dev) != TX_OK ||
+            scratch_get(static_cast<size_t>(n) * (fn.part_bytes + sp.tpp * nwt * 4), stream, &ws) != hipSuccess) {
+            (void)hipGetLastError();
+            sp.parts = 1;
+        }
+        sp.ws = static_cast<uint8_t*>(ws.p);
+    }
+    if (sp.parts > 1) {
+        void* args[] = {&a, &sp};
+        const dim3 grid(static_cast<uint32_t>(a.ndm) * static_cast<uint32_t>(sp.parts));
+        const size_t lds = static_cast<size_t>(sp.tpp) * nwt * 4;
+        const int prof = prof_begin(TX_KERNEL_BOXCAR, stream);
+        hipError_t e = hipLaunchKernel(fn.scan, grid, dim3(kThreads), args, lds, stream);
+        if (e == hipSuccess) e = hipLaunchKernel(fn.finish, grid, dim3(kThreads), args, lds, stream);
+        if (e == hipSuccess) e = hipGetLastError();
+        prof_end(prof, stream);
+        const hipError_t f = scratch_put(&ws, stream);
+        return e != hipSuccess ? e : f;
+    }
     if (a.want_cands) {
         hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, stream, a.count);
         const hipError_t e = hipGetLastError();

@@ -1,7 +1,7 @@
-"""The matched filter against the oracle where equal sums compete: few and many tiles
-(4096 starts each), the earliest of equal peaks in different lanes, wavefronts
-and tiles, candidates in many tiles and up to the row's end, unaligned rows,
-and a capture."""
+"""The matched filter against the oracle where equal sums compete and rows are
+split over workgroups: few and many tiles (4096 starts each), the earliest of
+equal peaks in different lanes, wavefronts, tiles and parts, candidates in many tiles and up to the row's end, unaligned rows,
+and a capture (which is not split)."""
 
 import numpy as np
 import pytest
