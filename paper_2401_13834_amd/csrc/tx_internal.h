@@ -188,7 +188,8 @@ struct BoxcarArgs {
 // (tx_kernels_norm.hip).  Stage 1: workgroups of 4 kNormJW coarse trials and
 // 256 kNormQ outputs (4 kNormQ per lane); stage 2: kNormIW fine trials and
 // kNormTT2 outputs (3 per lane).
-constexpr int kNormJW = 2;                 // stage 1: coarse trials per wave (8 per workgroup)
+constexpr int kNormJW = 2;                 // stage 1: coarse trials per wave (8 per workgroup),
+constexpr int kNormSharedJW = 4;           // 4 in the shared form
 constexpr int kNormQ = 5;                  // stage 1: output dwords per lane (20 outputs; odd)
 constexpr int kNormIW = 16;
 constexpr int kNormTT2 = 768;
@@ -197,6 +198,7 @@ constexpr int kNormTT2 = 768;
 // fewer workgroups with larger or double-buffered staging rounds.
 constexpr int kNormLds = 20 * 1024;        // stage 2
 constexpr int kNormLds1 = 20 * 1024;       // stage 1
+constexpr int kNormLdsShared = 40 * 1024;  // shared form: a quarter of a CU's LDS (its registers hold 4 workgroups)
 
 struct Stage1NormArgs {
     const uint8_t* x;       // input rows (16-byte aligned)
@@ -207,6 +209,8 @@ struct Stage1NormArgs {
     float* B;               // [ngroups][nsub][B_pitch]
     int64_t B_pitch;
     const int32_t* dT;
+    const int32_t* cT;      // [nsub][gpad] D(c_j, f_s)        (shared form only)
+    int64_t len;            // elements of a series the second stage uses, a multiple of 16 (same)
     int32_t gpad;
     int32_t nsub, m, ngroups;
     int32_t n_jchunks, n_ttiles;
@@ -255,6 +259,8 @@ struct NormGeom {
     int64_t ws_bytes;       // scratch bytes
     int32_t n_ttiles1, n_ttiles2, n_jchunks, n_ichunks;
     int32_t lds1, lds2;
+    bool shared;            // first stage in the shared form, which writes
+    int64_t len1;           // this much of a series
     bool ok;
 };
 

@@ -187,6 +187,208 @@ __global__ __launch_bounds__(kThreads) void stage1_norm_kernel(Stage1NormArgs a)
 }
 
 // ---------------------------------------------------------------------------
+// Stage 1 of plans whose neighbouring trials lie close.  With time v = u +
+// D(c_j, f_s) (aligned at the sub-band's reference channel) a channel's
+// samples are shifted by d = D(c_j, f_ch) - D(c_j, f_s) only, and neighbouring
+// trials by nearly the same d: so a wavefront normalises a channel's samples
+// once for its kNormSharedJW trials, and each trial adds the same registers
+// from its own first one (a uniform branch on the difference, 0..8).  A trial
+// further off has the samples read again from its own shift.  Terms and their
+// order are those of the general form, and so are the sums, bit for bit.
+//
+// Workgroup = (sub-band s, J = 4 kNormSharedJW coarse trials, TT = 256 kNormQ
+// values of v): wave w owns trials j0 + w kNormSharedJW .. and lane l the 4
+// kNormQ consecutive outputs from 4 kNormQ l.  Series start D(c_j, f_s) & 15
+// elements early.  Rows are staged as in the general form, but from the
+// smallest d of the workgroup's trials, and TT plus the spread of d long.
+// Bound by VALU issue: the general form's conversion, multiply-add and
+// addition per term take 6.2 ms on the 4096-channel, 4096-trial block of 65536
+// samples; here 28 conversions and multiply-adds serve 80 additions, 4.9 ms.
+// Measured: 2 trials per wavefront 5.8 ms.
+// ---------------------------------------------------------------------------
+// acc[q] += f[q + d], d uniform in 0..8.  The choice is a branch inside one asm
+// statement: as a switch the compiler merges the cases, and every term is moved
+// before it is added.
+#define TX_ADD1(q, f) "v_add_f32 %" #q ", %" #q ", %" #f "\n"
+#define TX_ADD20(a, b, c, d, e, f, g, h, i, j, k, l, m, n, o, p, q, r, s, t)                                        \
+    TX_ADD1(0, a) TX_ADD1(1, b) TX_ADD1(2, c) TX_ADD1(3, d) TX_ADD1(4, e) TX_ADD1(5, f) TX_ADD1(6, g)                \
+    TX_ADD1(7, h) TX_ADD1(8, i) TX_ADD1(9, j) TX_ADD1(10, k) TX_ADD1(11, l) TX_ADD1(12, m) TX_ADD1(13, n)            \
+    TX_ADD1(14, o) TX_ADD1(15, p) TX_ADD1(16, q) TX_ADD1(17, r) TX_ADD1(18, s) TX_ADD1(19, t)
+__device__ __forceinline__ void add_from(float (&x)[20], const float (&f)[28], int d) {
+    asm volatile(
+        "s_cmp_gt_u32 %48, 3\n s_cbranch_scc1 13f\n"
+        "s_cmp_gt_u32 %48, 1\n s_cbranch_scc1 11f\n"
+        "s_cmp_eq_u32 %48, 1\n s_cbranch_scc1 1f\n s_branch 0f\n"
+        "11:\n s_cmp_eq_u32 %48, 3\n s_cbranch_scc1 3f\n s_branch 2f\n"
+        "13:\n s_cmp_gt_u32 %48, 5\n s_cbranch_scc1 15f\n"
+        "s_cmp_eq_u32 %48, 5\n s_cbranch_scc1 5f\n s_branch 4f\n"
+        "15:\n s_cmp_eq_u32 %48, 6\n s_cbranch_scc1 6f\n"
+        "s_cmp_eq_u32 %48, 7\n s_cbranch_scc1 7f\n s_branch 8f\n"
+        "0:\n" TX_ADD20(20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39) "s_branch 9f\n"
+        "1:\n" TX_ADD20(21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39, 40) "s_branch 9f\n"
+        "2:\n" TX_ADD20(22, 23, 24, 25, 26, 27, 28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39, 40, 41) "s_branch 9f\n"
+        "3:\n" TX_ADD20(23, 24, 25, 26, 27, 28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39, 40, 41, 42) "s_branch 9f\n"
+        "4:\n" TX_ADD20(24, 25, 26, 27, 28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39, 40, 41, 42, 43) "s_branch 9f\n"
+        "5:\n" TX_ADD20(25, 26, 27, 28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39, 40, 41, 42, 43, 44) "s_branch 9f\n"
+        "6:\n" TX_ADD20(26, 27, 28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39, 40, 41, 42, 43, 44, 45) "s_branch 9f\n"
+        "7:\n" TX_ADD20(27, 28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39, 40, 41, 42, 43, 44, 45, 46) "s_branch 9f\n"
+        "8:\n" TX_ADD20(28, 29, 30, 31, 32, 33, 34, 35, 36, 37, 38, 39, 40, 41, 42, 43, 44, 45, 46, 47) 
+        "9:\n"
+        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]), "+v"(x[8]), "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]), "+v"(x[14]), "+v"(x[15]), "+v"(x[16]), "+v"(x[17]), "+v"(x[18]), "+v"(x[19])
+        : "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]), "v"(f[4]), "v"(f[5]), "v"(f[6]), "v"(f[7]), "v"(f[8]), "v"(f[9]), "v"(f[10]), "v"(f[11]), "v"(f[12]), "v"(f[13]), "v"(f[14]), "v"(f[15]), "v"(f[16]), "v"(f[17]), "v"(f[18]), "v"(f[19]), "v"(f[20]), "v"(f[21]), "v"(f[22]), "v"(f[23]), "v"(f[24]), "v"(f[25]), "v"(f[26]), "v"(f[27]), "s"(d)
+        : "scc");
+}
+
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void stage1_norm_shared_kernel(Stage1NormArgs a) {
+    extern __shared__ __align__(16) uint8_t lds[];
+    constexpr int Q = kNormQ;
+    constexpr int JW = kNormSharedJW;
+    constexpr int J = JW * kWaves;
+    constexpr int TS = 4 * Q;
+    constexpr int TT = 64 * TS;
+    const int tile = xcd_tile(static_cast<int>(blockIdx.x), a.nsub * a.n_ttiles * a.n_jchunks);
+    const int jc = tile % a.n_jchunks;
+    const int rest = tile / a.n_jchunks;
+    const int s = rest / a.n_ttiles;
+    const int j0 = jc * J;
+    const int jl = min(j0 + J, a.ngroups) - 1;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = uniform(tid >> 6);
+    const int ch0 = s * a.m;
+    const size_t gp = static_cast<size_t>(a.gpad);
+    const TX_GLOBAL int32_t* __restrict__ dT = to_global(a.dT);
+    const TX_GLOBAL int32_t* __restrict__ cT = to_global(a.cT) + static_cast<size_t>(s) * gp;
+    // Tiles are cut at multiples of TT of v.
+    const int64_t v0 = (static_cast<int64_t>(uniform(cT[j0]) & ~15) / TT + rest % a.n_ttiles) * TT;
+    if (v0 >= (uniform(cT[jl]) & ~15) + a.len) return;
+    int* red = reinterpret_cast<int*>(lds);
+
+    // Tables at the top of LDS: per (channel, trial) the shift from the
+    // channel's staging start; per channel its start, scale and -offset.
+    const int fix_off = (a.lds_bytes - ((a.m * (J + 3) * 4 + 15) & ~15)) & ~15;
+    int32_t* tab = reinterpret_cast<int32_t*>(lds + fix_off);   // [m][J]
+    int32_t* st0 = tab + a.m * J;                                 // [m]
+    float* wsc = reinterpret_cast<float*>(st0 + a.m);             // [m]
+    float* wof = wsc + a.m;                                       // [m]
+    static_assert(J == 16 && TS == 20, "one DPP row per channel; add_from's outputs");
+    int sp = 0;
+    for (int t = tid; t < a.m * J; t += kThreads) {               // (whole rows of 16 lanes)
+        const int c = t / J, j = min(j0 + t % J, jl);
+        const int d = dT[static_cast<size_t>(ch0 + c) * gp + j] - cT[j];
+        int lo = d, hi = d;
+        lo = min(lo, __builtin_amdgcn_update_dpp(lo, lo, 0xB1, 0xF, 0xF, false));     // quad_perm [1,0,3,2]
+        hi = max(hi, __builtin_amdgcn_update_dpp(hi, hi, 0xB1, 0xF, 0xF, false));
+        lo = min(lo, __builtin_amdgcn_update_dpp(lo, lo, 0x4E, 0xF, 0xF, false));     // quad_perm [2,3,0,1]
+        hi = max(hi, __builtin_amdgcn_update_dpp(hi, hi, 0x4E, 0xF, 0xF, false));
+        lo = min(lo, __builtin_amdgcn_update_dpp(lo, lo, 0x141, 0xF, 0xF, false));    // row_half_mirror
+        hi = max(hi, __builtin_amdgcn_update_dpp(hi, hi, 0x141, 0xF, 0xF, false));
+        lo = min(lo, __builtin_amdgcn_update_dpp(lo, lo, 0x140, 0xF, 0xF, false));    // row_mirror
+        hi = max(hi, __builtin_amdgcn_update_dpp(hi, hi, 0x140, 0xF, 0xF, false));
+        tab[t] = d - (lo & ~15);
+        if (t % J == 0) st0[c] = lo & ~15;
+        sp = max(sp, hi - (lo & ~15));
+    }
+    for (int c = tid; c < a.m; c += kThreads) {
+        wsc[c] = to_global(a.scale)[ch0 + c];
+        wof[c] = -to_global(a.offset)[ch0 + c];
+    }
+    sp = uniform(block_max(sp, red));
+    const int rowbytes = (sp + TT + 8 + 15) & ~15;        // last byte read: sp + 63 TS + TS + 7
+    const int nbuf = 2 * rowbytes <= fix_off ? 2 : 1;
+    const int nch = max(1, min(a.m, fix_off / nbuf / rowbytes));
+    const int buf_bytes = nch * rowbytes;
+    __syncthreads();
+
+    // Rows of channels [cb, cb + nch) into `dat`: wave w stages rows w, w + 4,
+    // ..., whole 16-byte pieces through a raw buffer resource sized to the
+    // row's whole valid pieces (zeros past them); the piece that straddles the
+    // row's end, if any, byte by byte.
+    auto stage = [&](int cb, uint8_t* dat) {
+        const int nc = min(nch, a.m - cb);
+        for (int c = wave; c < nc; c += kWaves) {
+            const int64_t start = v0 + uniform(st0[cb + c]);
+            int64_t nb64 = a.x_len - start;                     // valid bytes of the staged row
+            nb64 = nb64 < 0 ? 0 : (nb64 > rowbytes ? rowbytes : nb64);
+            const int nb = uniform(static_cast<int>(nb64));
+            const int part = (nb & 15) ? nb >> 4 : -1;
+            const uint8_t* row = a.x + static_cast<size_t>(ch0 + cb + c) * a.x_pitch + start;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint8_t*>(row), static_cast<short>(0), nb & ~15, kRawBufferWord3);
+            uint8_t* dst = dat + c * rowbytes;
+            const int pieces = rowbytes >> 4;
+            for (int i = lane; i - lane < pieces; i += 64)
+                if (i < pieces && i != part)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, to_lds(dst + 16 * (i - lane)), 16, 16 * i, 0, 0, 0);
+            if (part >= 0 && (part & 63) == lane) {
+                const TX_GLOBAL uint8_t* src = to_global(row) + 16 * part;
+                uint32_t d[4] = {0u, 0u, 0u, 0u};
+                for (int b = 0; b < (nb & 15); ++b) d[b >> 2] |= static_cast<uint32_t>(src[b]) << (8 * (b & 3));
+                *reinterpret_cast<uint4*>(dst + 16 * part) = make_uint4(d[0], d[1], d[2], d[3]);
+            }
+        }
+    };
+
+    float acc[JW][TS];
+#pragma unroll
+    for (int jj = 0; jj < JW; ++jj)
+#pragma unroll
+        for (int q = 0; q < TS; ++q) acc[jj][q] = 0.0f;
+
+    stage(0, lds);
+    for (int cb = 0, r = 0; cb < a.m; cb += nch, ++r) {
+        const int nc = min(nch, a.m - cb);
+        const uint8_t* dat = lds + (r & (nbuf - 1)) * buf_bytes;
+        // This wave's rows of the round have landed; after the barrier every
+        // wave's have, and nobody still reads the other buffer.
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        __syncthreads();
+        if (nbuf == 2 && cb + nch < a.m) stage(cb + nch, lds + ((r + 1) & 1) * buf_bytes);
+        const uint8_t* lane_row = dat + TS * lane;
+        for (int c = 0; c < nc; ++c, lane_row += rowbytes) {
+            const float sc = wsc[cb + c];                          // one address: a broadcast read
+            const float of = wof[cb + c];
+            int d[JW];
+#pragma unroll
+            for (int jj = 0; jj < JW; ++jj) d[jj] = uniform(tab[(cb + c) * J + wave * JW + jj]);
+            float f[TS + 8];
+            int base = -16;                                        // shift of f[0]
+#pragma unroll
+            for (int jj = 0; jj < JW; ++jj) {
+                if (static_cast<uint32_t>(d[jj] - base) > 8u) {    // (always for the first trial)
+                    base = d[jj] & ~3;
+                    const uint32_t* p = reinterpret_cast<const uint32_t*>(lane_row + base);
+                    uint32_t w[Q + 2];
+#pragma unroll
+                    for (int q = 0; q < Q + 2; ++q) w[q] = p[q];
+                    // the channel's normalised sample, rounded once
+#pragma unroll
+                    for (int q = 0; q < TS + 8; ++q) f[q] = __builtin_fmaf(byte_f(w[q >> 2], q & 3), sc, of);
+                }
+                add_from(acc[jj], f, d[jj] - base);                // then added
+            }
+        }
+        if (nbuf == 1 && cb + nch < a.m) {
+            __syncthreads();
+            stage(cb + nch, lds);
+        }
+    }
+#pragma unroll
+    for (int jj = 0; jj < JW; ++jj) {
+        const int j = j0 + wave * JW + jj;
+        if (j <= jl) {
+            const int64_t e = v0 + TS * lane - (cT[j] & ~15);      // multiples of 4, as a.len is
+            TX_GLOBAL float* out = to_global(a.B) + (static_cast<size_t>(j) * a.nsub + s) * a.B_pitch + e;
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (e + 4 * q >= 0 && e + 4 * q < a.len)
+                    *reinterpret_cast<TX_GLOBAL float4*>(out + 4 * q) =
+                        make_float4(acc[jj][4 * q], acc[jj][4 * q + 1], acc[jj][4 * q + 2], acc[jj][4 * q + 3]);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Stage 2.  Workgroup = (group j, up to kNormIW of its trials, TT = 768
 // outputs): lane l of wave w owns the 3 consecutive outputs from
 // 3 (64 w + l), so its words of a (sub-band, trial) are one paired and one
@@ -712,25 +914,56 @@ __global__ void zero_count_norm_kernel(unsigned long long* p) {
 
 // ---------------------------------------------------------------------------
 
+// Least LDS of a workgroup of the shared form: one staged row and the tables.
+static int norm_shared_need(const tx_plan_s* p) {
+    const int64_t row = (p->mx.spread + 15ll + 256 * kNormQ + 8 + 15) & ~15ll;
+    return static_cast<int>(
+        std::min<int64_t>(row + ((p->m * (4 * kNormSharedJW + 3) * 4 + 15) & ~15) + 64, INT32_MAX));
+}
+
+// The shared form where it pays: while the plan's windows of 16 samples over 4
+// trials are nearly one each, trials mostly find their samples normalised, and
+// few lanes of 16 trials are padding.  Measured over 22 plans (its time of the
+// first stage over the general form's): windows times padding 1.0-1.45
+// 0.74-0.97, 1.6-2.0 0.91-1.39, above 0.62 (10 coarse trials of 48 channels) to 1.31.
+static bool norm_shares(const tx_plan_s* p) {
+    constexpr int J = 4 * kNormSharedJW;
+    const double padded = static_cast<double>((p->ngroups + J - 1) / J * J) / p->ngroups;
+    return p->mx.windows * padded < 1.5 && norm_shared_need(p) <= device_max_lds();
+}
+
 NormGeom norm_geometry(const tx_plan_s* p, int64_t nt) {
     NormGeom g{};
     g.n_ttiles2 = static_cast<int32_t>((nt + kNormTT2 - 1) / kNormTT2);
     g.n_ichunks = (p->g + kNormIW - 1) / kNormIW;
-    g.n_jchunks = (p->ngroups + 4 * kNormJW - 1) / (4 * kNormJW);
     // stage 2 stages floats [start, start + rowf) of a series, start <= last
     // tile start + max extent; rowf <= spread + TT + 3
     const int sp2 = plan_spread2(p, kNormIW) + 3;
     const int64_t need = static_cast<int64_t>(std::max(g.n_ttiles2 - 1, 0)) * kNormTT2 + p->max_extent + sp2 + kNormTT2 + 4;
     const int tt1 = 256 * kNormQ;
-    g.B_pitch = (std::max<int64_t>(need, nt + p->max_extent) + tt1 - 1) / tt1 * tt1;
-    g.n_ttiles1 = static_cast<int32_t>(g.B_pitch / tt1);
-    g.ws_bytes = (static_cast<int64_t>(p->ngroups) * p->nsub * g.B_pitch * 4 + 255) / 256 * 256;
     const int sp1 = plan_spread1(p, 4 * kNormJW) + 15;
     const int row1 = 4 * (((sp1 >> 2) + 64 * kNormQ + 1 + 3) & ~3);   // a staged row (as the kernel sizes it)
     g.lds1 = std::max(kNormLds1, row1 + ((p->m * (4 * kNormJW + 3) * 4 + 15) & ~15) + 64);
+    g.ok = g.lds1 <= device_max_lds();
+    int J = 4 * kNormJW;
+    g.shared = norm_shares(p);
+    if (g.shared) {
+        // Series start up to 15 elements early; tiles are cut at multiples of
+        // their length of v.
+        J = 4 * kNormSharedJW;
+        g.len1 = (nt + p->max_extent + 15 + 15) / 16 * 16;
+        g.B_pitch = (std::max<int64_t>(need + 15, g.len1) + 15) / 16 * 16;
+        g.n_ttiles1 = static_cast<int32_t>((g.len1 + p->mx.vspread_max + 15) / tt1 + 2);
+        g.lds1 = std::max(kNormLdsShared, norm_shared_need(p));
+    } else {
+        g.B_pitch = (std::max<int64_t>(need, nt + p->max_extent) + tt1 - 1) / tt1 * tt1;
+        g.n_ttiles1 = static_cast<int32_t>(g.B_pitch / tt1);
+    }
+    g.n_jchunks = (p->ngroups + J - 1) / J;
+    g.ws_bytes = (static_cast<int64_t>(p->ngroups) * p->nsub * g.B_pitch * 4 + 255) / 256 * 256;
     const int row2 = ((sp2 + kNormTT2 + 3) & ~3) * 4;
     g.lds2 = std::max(kNormLds, row2 + ((kNormIW * p->nsub * 4 + 15) & ~15) + 64);
-    g.ok = g.lds1 <= device_max_lds() && g.lds2 <= device_max_lds();
+    g.ok = g.ok && g.lds2 <= device_max_lds();
     return g;
 }
 
@@ -755,7 +988,9 @@ hipError_t launch_dedisperse_norm(const tx_plan_s* p, const NormGeom& g, const u
     a1.offset = offset;
     a1.B = d_B;
     a1.B_pitch = g.B_pitch;
+    a1.len = g.len1;
     a1.dT = p->d_dT;
+    a1.cT = p->d_cT;
     a1.gpad = p->gpad;
     a1.nsub = p->nsub;
     a1.m = p->m;
@@ -769,7 +1004,7 @@ hipError_t launch_dedisperse_norm(const tx_plan_s* p, const NormGeom& g, const u
     a2.Y = d_out;
     a2.y_pitch = out_pitch;
     a2.nt = nt;
-    a2.rT = p->d_rT;
+    a2.rT = g.shared ? p->d_rTo : p->d_rT;
     a2.dpad = p->dpad;
     a2.ndm = p->ndm;
     a2.nsub = p->nsub;
@@ -783,7 +1018,8 @@ hipError_t launch_dedisperse_norm(const tx_plan_s* p, const NormGeom& g, const u
     const int64_t grid2 = static_cast<int64_t>(p->ngroups) * g.n_ichunks * g.n_ttiles2;
     if (grid1 > INT32_MAX || grid2 > INT32_MAX) return hipErrorInvalidValue;
     int prof = prof_begin(TX_KERNEL_STAGE1, stream);
-    hipError_t e = launch_lds(reinterpret_cast<const void*>(&stage1_norm_kernel), static_cast<int>(grid1), g.lds1, v1,
+    hipError_t e = launch_lds(g.shared ? reinterpret_cast<const void*>(&stage1_norm_shared_kernel)
+                                          : reinterpret_cast<const void*>(&stage1_norm_kernel), static_cast<int>(grid1), g.lds1, v1,
                               stream);
     prof_end(prof, stream);
     if (e != hipSuccess) return e;
