@@ -685,14 +685,17 @@ static bool mx_fits(const tx_plan_s* p, int64_t nt) {
 // output pass to be paid by few products.  A plan of few coarse trials leaves
 // CUs idle under the general form, whose tiles are twice as long, and gains
 // longer.  Measured over 80 plans, blocks of 4096 to 49152 samples, its time
-// of the first stage over the general form's: 100 coarse trials or more, estimates of
-// 1.2-1.6 0.45-0.78, 1.6-2.0 0.52-0.94, 2.0-2.35 0.62-1.00, 2.35-2.9 0.96-1.12,
-// above 1.03-2.3; fewer trials, 1.3-3.3 0.32-0.96 (one of 20 1.07), above
-// 0.83-2.25 (mean 1.3).  The plan alone decides, so that scratch sized for a
-// long block serves shorter ones.
+// of the first stage over the general form's: 100 coarse trials or more,
+// estimates of 1.3-1.8 0.32-0.80, 1.8-2.2 0.52-0.95, 2.2-3.0 0.80-1.12, above
+// 1.03-2.3; at 2.25 (256 channels in 16 sub-bands, 2726 trials) 0.85, yet calls
+// one after the other took 447 us against 435, since the general form runs at
+// higher clocks.  Fewer trials (10 / m), 1.3-3.3 0.32-0.96 (one of 20 1.07),
+// above 0.83-2.25 (mean 1.3).  The plan alone decides, so that scratch sized
+// for a long block serves shorter ones.
 static bool mx_pays(const tx_plan_s* p) {
     const double padded = static_cast<double>((p->ngroups + 15) / 16 * 16) / p->ngroups;
-    return (p->mx.windows + 10.0 / p->m) * padded < (p->ngroups < 100 ? 3.3 : 2.35);
+    if (p->ngroups < 100) return (p->mx.windows + 10.0 / p->m) * padded < 3.3;
+    return (p->mx.windows + 20.0 / p->m) * padded < 2.2;
 }
 
 bool default_stage1(const Tiles& t) { return t.s1 < 0 || t.s1 >= kNS1; }
