@@ -286,18 +286,23 @@ __device__ __forceinline__ void cand_tile(const BoxcarArgs& a, BoxShared<NWT>& s
             pass |= S >= thr && 256 * j <= lim ? 1u << j : 0u;
         }
     }
-    const uint32_t n = __popc(pass);
-    const uint32_t incl = wave_incl_sum(n);
-    const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+    // Places in the order of the starts 256 j + lane.
+    uint32_t total = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) total += static_cast<uint32_t>(__popcll(__ballot(pass >> j & 1u)));
     if (total == 0) return;
     unsigned long long base = 0;
     if ((tid & 63) == 0) base = atomicAdd(a.count, static_cast<unsigned long long>(total));
     base = __shfl(base, 0);
-    unsigned long long slot = base + (incl - n);
 #pragma unroll 1
-    for (; pass; pass &= pass - 1, ++slot) {
-        if (static_cast<long long>(slot) >= a.cap) break;
-        const int e = tid + 256 * (__ffs(pass) - 1);
+    for (int j = 0; j < 16; ++j) {
+        const unsigned long long in = __ballot(pass >> j & 1u);
+        const unsigned long long slot =
+            base + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(in >> 32),
+                                             __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(in), 0u));
+        base += static_cast<unsigned long long>(__popcll(in));
+        if (!(pass >> j & 1u) || static_cast<long long>(slot) >= a.cap) continue;
+        const int e = tid + 256 * j;
         const uint32_t pt = sh.P[e];
         double bs = 0.0;
         int bw = -1;
