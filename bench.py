@@ -43,13 +43,13 @@ MEASURED_READ_BYTES_PER_S = 5.94e12
 MEASURED_WRITE_BYTES_PER_S = 1.0 / (2.0 / MEASURED_COPY_BYTES_PER_S - 1.0 / MEASURED_READ_BYTES_PER_S)
 
 
-KERNEL_SOURCES = {"stage1": ("tx_kernels_dedisp.hip",), "stage2": ("tx_kernels_dedisp.hip",),
+KERNEL_SOURCES = {"stage1": ("tx_kernels_dedisp.hip", "tx_stage1_mx.h"), "stage2": ("tx_kernels_dedisp.hip",),
                   "boxcar": ("tx_kernels_boxcar.hip",), "transpose": ("tx_kernels_transpose.hip",),
                   "stats": ("tx_kernels_stats.hip",), "downsample2": ("tx_kernels_downsample.hip",),
                   "downsample4": ("tx_kernels_downsample.hip",),
                   # the batch launch: its persistent dedispersion and boxcar kernels,
                   # and the plan code that picks each beam's sub-band count
-                  "batch": ("tx_kernels_dedisp.hip", "tx_kernels_boxcar.hip", "tx_plan.cpp")}
+                  "batch": ("tx_kernels_dedisp.hip", "tx_stage1_mx.h", "tx_kernels_boxcar.hip", "tx_plan.cpp")}
 
 
 def kernel_source_hash(kernel):

@@ -50,8 +50,9 @@ typedef enum tx_status {
 /* Human-readable name of a status code.  Never NULL. */
 const char* tx_status_str(tx_status s);
 
-/* Return the stream-ordered scratch that libtx calls have freed on the
- * current device to the system (libtx keeps it pooled for reuse otherwise).
+/* Return the scratch that libtx calls are done with on the current device to
+ * the system (libtx keeps it for reuse otherwise: buffers of up to 64 MB, at
+ * most 512 MB of them, and the device's stream-ordered pool).
  * Synchronises the device.  Errors: TX_EDEVICE. */
 tx_status tx_pool_trim(void);
 
@@ -190,7 +191,8 @@ tx_status tx_dedisperse_ws_size(tx_plan_t plan, int64_t nt, int64_t* bytes);
  *   stream    HIP stream for all work.
  *
  * Every value is an exact integer sum (bit-exact for any tiling).  Scratch for
- * the first stage comes from the device's stream-ordered memory pool and is
+ * the first stage is kept from an earlier call (up to 64 MB; tx_pool_trim
+ * frees it) or comes from the device's stream-ordered memory pool and is
  * returned to it on the same stream.
  * Errors: TX_EINVAL, TX_ESTATE (host-only plan or another device current),
  * TX_ENOMEM, TX_EDEVICE.
@@ -321,8 +323,8 @@ tx_status tx_norm_weights(const uint64_t* sums, int32_t nchan, int64_t nt, int32
  * u + D(c_j, f_ch) (the plan's offsets).  Summed in float32 in that order, a
  * value differs from the exact sum by at most (m + nsub + 1) * 2^-24 times
  * the sum of the absolute normalised samples it adds (m = channels per
- * sub-band).  Scratch (4 bytes per first-stage sample) comes from the
- * device's stream-ordered pool.  The plan's channel mask and tiles do not
+ * sub-band).  Scratch (4 bytes per first-stage sample) comes as
+ * tx_dedisperse's.  The plan's channel mask and tiles do not
  * apply (a dropped channel is one with scale = offset = 0).  Errors:
  * TX_EINVAL, TX_ESTATE, TX_ENOMEM, TX_ENOTSUP (a staged row does not fit the
  * device's LDS), TX_EDEVICE.
@@ -375,7 +377,7 @@ tx_status tx_ranges_input_len(tx_ranges_t r, int64_t nt, int64_t* need);
  * in_pitch >= tx_ranges_input_len(nt).  Range r writes plans[r]'s ndm rows of
  * nt / factors[r] samples to d_outs[r] (out_pitches[r] elements per row, as
  * for tx_dedisperse).  Each distinct factor > 1 downsamples the block once
- * into a buffer from the device's stream-ordered pool, returned on `stream`.
+ * into scratch that comes as tx_dedisperse's.
  * Every output equals tx_dedisperse of plans[r] on tx_downsample's output.
  * Errors: TX_EINVAL, TX_ESTATE, TX_ENOMEM, TX_ENOTSUP, TX_EDEVICE.
  */
