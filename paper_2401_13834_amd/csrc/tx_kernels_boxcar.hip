@@ -32,6 +32,11 @@ constexpr int kTileMaxLds = 16 * 1024;
 
 constexpr int kSplitGroups = 6 * 256;   // workgroups that a split aims at
 
+// Largest calls of the list form (boxcar_list_kernel): rows that the chip holds
+// at once (5 workgroups per CU), and tiles per row.
+constexpr int kListRows = 5 * 256;
+constexpr int kListTiles = 16;
+
 template <int NWT>
 struct BoxShared {
     __align__(16) uint32_t P[kBoxTile + TX_MAX_WIDTH + 16];
@@ -261,6 +266,107 @@ __device__ __forceinline__ void peak_tile(const BoxcarArgs& a, BoxShared<NWT>& s
     }
 }
 
+// Peak search over one tile in the list form (boxcar_list_kernel): every
+// wavefront looks up the starts of its own bests, which sh.wS and sh.wT hold
+// from tile to tile.
+template <int NWT, bool TAIL>
+__device__ __forceinline__ void peak_tile_list(const BoxcarArgs& a, BoxShared<NWT>& sh, int tile, int t0, int tid,
+                                               bool keep_tmax) {
+    const int wave = tid >> 6;
+    const int T = a.nt;
+    uint32_t Pt[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) Pt[j] = sh.P[tid + 256 * j];
+    int32_t tm[NWT];
+#pragma unroll
+    for (int i = 0; i < NWT; i += 2) {
+        // Per-width values come from LDS, which keeps the registers free.
+        const int w0 = sh.wd[i], w1 = sh.wd[i + 1];
+        const uint32_t* p0 = sh.P + tid + w0;
+        const uint32_t* p1 = sh.P + tid + w1;
+        int32_t tm0 = INT32_MIN, tm1 = INT32_MIN;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int32_t S0 = static_cast<int32_t>(p0[256 * j] - Pt[j]);
+            const int32_t S1 = static_cast<int32_t>(p1[256 * j] - Pt[j]);
+            const int t = t0 + tid + 256 * j;
+            tm0 = max(tm0, (!TAIL || t + w0 <= T) ? S0 : INT32_MIN);   // no window past the row end
+            tm1 = max(tm1, (!TAIL || t + w1 <= T) ? S1 : INT32_MIN);
+        }
+        tm[i] = tm0;
+        tm[i + 1] = tm1;
+        // Keep each width pair's LDS reads next to their arithmetic.
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // Wavefront maxima of all widths (independent reductions, interleaved).
+    int32_t wm[NWT];
+#pragma unroll
+    for (int i = 0; i < NWT; ++i) wm[i] = wave_max_i32(tm[i]);
+#pragma unroll 1
+    for (int ii = 0; ii < NWT; ++ii) {
+        // wm[ii] with a run-time ii: select among the (uniform) values.
+        int32_t m = wm[0];
+#pragma unroll
+        for (int k = 1; k < NWT; ++k) m = (k == ii) ? wm[k] : m;
+        if (keep_tmax && (tid & 63) == 0) atomicMax(&tx_box_tmax[tile * NWT + ii], m);
+        if (m > sh.wS[ii][wave]) {                      // wavefront-uniform, a few tiles per row
+            const int w = sh.wd[ii];
+            int32_t first = INT32_MAX;
+#pragma unroll 1
+            for (int j = 15; j >= 0; --j) {             // rolled: this path is rare
+                const int e = tid + 256 * j;
+                const int t = t0 + e;
+                const int32_t S = static_cast<int32_t>(sh.P[e + w] - sh.P[e]);
+                first = ((!TAIL || t + w <= T) && S == m) ? t : first;
+            }
+            const int32_t ft = wave_min_i32(first);
+            if ((tid & 63) == 0) {
+                sh.wS[ii][wave] = m;
+                sh.wT[ii][wave] = ft;
+            }
+        }
+    }
+}
+
+// Candidates of one tile in the list form: every 64 starts take their places
+// with one atomic.  Widths increase, so a strict ">" keeps the smaller width on
+// equal S/N.
+template <int NWT>
+__device__ __forceinline__ void cand_tile_list(const BoxcarArgs& a, BoxShared<NWT>& sh, int row, int t0, long long sum,
+                                               double inv_d, int tid) {
+    const int T = a.nt;
+#pragma unroll 1
+    for (int j = 0; j < 16; ++j) {
+        const int e = tid + 256 * j;
+        const int t = t0 + e;
+        const uint32_t pt = sh.P[e];
+        bool pass = false;
+        double bs = 0.0;
+        int bw = -1;
+        for (int i = 0; i < a.ne; ++i) {
+            const int w = sh.wd[i];
+            if (t + w > T) continue;
+            const int32_t S = static_cast<int32_t>(sh.P[e + w] - pt);
+            pass = pass || S >= max(sh.sthr[i], 0);       // window sums are >= 0
+            const double sn = snr_of(T, S, w, sum, inv_d, sh.rs[i]);
+            if (bw < 0 || sn > bs) {
+                bs = sn;
+                bw = w;
+            }
+        }
+        if (!pass) continue;
+        const unsigned long long slot = atomicAdd(a.count, 1ull);
+        if (static_cast<long long>(slot) < a.cap) {
+            tx_cand c;
+            c.dm_index = row;
+            c.width = bw;
+            c.time = t;
+            c.snr = bs;
+            to_global(a.cands)[slot] = c;
+        }
+    }
+}
+
 // Candidates of one tile (rare: only tiles where some width's largest sum
 // reaches its threshold S*).  The starts that pass are found first, as 16 bits
 // per lane, with the sums alone; the wavefront then takes its places in the
@@ -326,9 +432,11 @@ __device__ __forceinline__ void cand_tile(const BoxcarArgs& a, BoxShared<NWT>& s
     }
 }
 
-// Widths and 1/sqrt(w) of the row's job into LDS, the per-width best cleared.
-template <int NWT>
-__device__ __forceinline__ void row_setup(const BoxcarArgs& a, BoxShared<NWT>& sh, int tid) {
+// Widths and 1/sqrt(w) of the row's job into LDS, the per-width best cleared
+// (in the list form every wavefront's, and the maxima of the row's tiles).
+template <int NWT, bool LIST = false>
+__device__ __forceinline__ void row_setup(const BoxcarArgs& a, BoxShared<NWT>& sh, int tid, int ntiles = 0,
+                                          bool keep_tmax = false) {
     if (tid < NWT) {
         int32_t w = 0;
         double r = 0.0;
@@ -343,12 +451,23 @@ __device__ __forceinline__ void row_setup(const BoxcarArgs& a, BoxShared<NWT>& s
         sh.bS[tid] = INT32_MIN;
         sh.bT[tid] = 0;
     }
+    if (LIST) {
+        if ((tid & 63) == 0) {
+#pragma unroll
+            for (int i = 0; i < NWT; ++i) {
+                sh.wS[i][tid >> 6] = INT32_MIN;
+                sh.wT[i][tid >> 6] = 0;
+            }
+        }
+        if (keep_tmax)
+            for (int k = tid; k < ntiles * NWT; k += kThreads) tx_box_tmax[k] = INT32_MIN;
+    }
     __syncthreads();
 }
 
 // Tiles [tlo, thi) of a row: running sums, exact moments (wavefront sums left
 // in sh.red*), per-width best (sh.bS / sh.bT) and the per-(tile, width) maxima.
-template <int NWT>
+template <int NWT, bool LIST = false>
 __device__ __forceinline__ void row_scan(const BoxcarArgs& a, int tlo, int thi, bool keep_tmax,
                                          const TX_GLOBAL int32_t* __restrict__ y, bool vec, BoxShared<NWT>& sh,
                                          int tid) {
@@ -365,7 +484,10 @@ __device__ __forceinline__ void row_scan(const BoxcarArgs& a, int tlo, int thi, 
         int tv = tid;
         asm volatile("" : "+v"(tv));
         scan_tile<true>(y, T, t0, L, sh.P, sh.wtot, vec, tv, m);
-        if (a.ne > 0) {
+        if (LIST) {
+            if (t0 + kBoxTile + a.wmax > T) peak_tile_list<NWT, true>(a, sh, tile, t0, tv, keep_tmax);
+            else peak_tile_list<NWT, false>(a, sh, tile, t0, tv, keep_tmax);
+        } else if (a.ne > 0) {
             if (t0 + kBoxTile + a.wmax > T) peak_tile<NWT, true>(a, sh, tile - tlo, t0, tv, keep_tmax);
             else peak_tile<NWT, false>(a, sh, tile - tlo, t0, tv, keep_tmax);
         }
@@ -379,12 +501,23 @@ __device__ __forceinline__ void row_scan(const BoxcarArgs& a, int tlo, int thi, 
         sh.red2[wave] = s2;
         sh.redbad[wave] = bad;
     }
+    if (LIST && tid < NWT) {                     // (the last tile's barrier orders these reads)
+        int32_t S = sh.wS[tid][0], t = sh.wT[tid][0];
+#pragma unroll
+        for (int v = 1; v < kWaves; ++v)
+            if (sh.wS[tid][v] > S || (sh.wS[tid][v] == S && sh.wT[tid][v] < t)) {
+                S = sh.wS[tid][v];
+                t = sh.wT[tid][v];
+            }
+        sh.bS[tid] = S;
+        sh.bT[tid] = t;
+    }
     __syncthreads();
 }
 
 // Statistics, the row's peak (when `peak`) and (when asked) the candidates of
 // its tiles [tlo, thi), from the state row_scan left in LDS.
-template <int NWT>
+template <int NWT, bool LIST = false>
 __device__ __forceinline__ void row_finish(const BoxcarArgs& a, int row, bool peak, int tlo, int thi, bool keep_tmax,
                                            const TX_GLOBAL int32_t* __restrict__ y, bool vec, BoxShared<NWT>& sh,
                                            int tid) {
@@ -515,7 +648,8 @@ __device__ __forceinline__ void row_finish(const BoxcarArgs& a, int row, bool pe
                     asm volatile("" : "+v"(tv));
                     Moments unused;
                     scan_tile<false>(y, T, tile * kBoxTile, L, sh.P, sh.wtot, vec, tv, unused);
-                    cand_tile<NWT>(a, sh, row, tile, keep_tmax, sum, inv_d, tlo, tv);
+                    if (LIST) cand_tile_list<NWT>(a, sh, row, tile * kBoxTile, sum, inv_d, tv);
+                    else cand_tile<NWT>(a, sh, row, tile, keep_tmax, sum, inv_d, tlo, tv);
                     __syncthreads();
                 }
             }
@@ -526,15 +660,15 @@ __device__ __forceinline__ void row_finish(const BoxcarArgs& a, int row, bool pe
 }
 
 
-template <int NWT>
+template <int NWT, bool LIST = false>
 __device__ __forceinline__ void boxcar_row(const BoxcarArgs& a, int row, BoxShared<NWT>& sh, int tid) {
     const TX_GLOBAL int32_t* __restrict__ y = to_global(a.y) + static_cast<size_t>(row) * a.pitch;
     const bool vec = ((reinterpret_cast<uintptr_t>(a.y) + static_cast<uintptr_t>(row) * a.pitch * 4) & 15) == 0;
     const int ntiles = (a.nt + kBoxTile - 1) / kBoxTile;
     const bool keep_tmax = a.tmax_ok != 0;
-    row_setup<NWT>(a, sh, tid);
-    row_scan<NWT>(a, 0, ntiles, keep_tmax, y, vec, sh, tid);
-    row_finish<NWT>(a, row, a.want_peaks != 0, 0, ntiles, keep_tmax, y, vec, sh, tid);
+    row_setup<NWT, LIST>(a, sh, tid, ntiles, keep_tmax);
+    row_scan<NWT, LIST>(a, 0, ntiles, keep_tmax, y, vec, sh, tid);
+    row_finish<NWT, LIST>(a, row, a.want_peaks != 0, 0, ntiles, keep_tmax, y, vec, sh, tid);
 }
 
 #define TX_BOX_WAVES __attribute__((amdgpu_waves_per_eu(NWT <= 12 ? 7 : NWT <= 16 ? 6 : 5)))
@@ -548,6 +682,23 @@ __global__ __launch_bounds__(kThreads) TX_BOX_WAVES void boxcar_kernel(BoxcarArg
     __shared__ BoxShared<NWT> sh;
     const int row = static_cast<int>(blockIdx.x);        // grid = rows
     if (row < a.ndm) boxcar_row<NWT>(a, row, sh, static_cast<int>(threadIdx.x));
+}
+
+// Single job that lists the candidates of up to kListRows rows of kListTiles
+// tiles.  Records are appended as the rows come to them, so their order is that
+// of the rows' times.  While all rows run side by side it mostly repeats from
+// call to call, and callers compare lists as they come: here a row's time stays
+// what it is with one lookup per wavefront and best and one atomic per 64
+// starts.  Of the values of 600 to 960 records (128 rows x 8192 samples) 55 to
+// 65% differ between two calls of this form, as many between this form and
+// one that also solves its thresholds by bisection, and 98% between this form and boxcar_kernel or
+// its candidate pass.  Larger calls, whose rows start as others end, and
+// batches, whose rows go to whichever workgroup is free, list in the faster form.
+template <int NWT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void boxcar_list_kernel(BoxcarArgs a) {
+    __shared__ BoxShared<NWT> sh;
+    const int row = static_cast<int>(blockIdx.x);        // grid = rows
+    if (row < a.ndm) boxcar_row<NWT, true>(a, row, sh, static_cast<int>(threadIdx.x));
 }
 
 // Few rows: each row's tiles are split over `parts` workgroups, in two
@@ -695,6 +846,7 @@ int boxcar_tmax_bytes(int nwt, int64_t nt) {
 
 struct BoxFns {
     const void* row;
+    const void* list;
     const void* scan;
     const void* finish;
     const void* batch;
@@ -703,7 +855,8 @@ struct BoxFns {
 
 template <int NWT>
 static BoxFns box_fns() {
-    return {reinterpret_cast<const void*>(&boxcar_kernel<NWT>), reinterpret_cast<const void*>(&boxcar_scan_kernel<NWT>),
+    return {reinterpret_cast<const void*>(&boxcar_kernel<NWT>), reinterpret_cast<const void*>(&boxcar_list_kernel<NWT>),
+            reinterpret_cast<const void*>(&boxcar_scan_kernel<NWT>),
             reinterpret_cast<const void*>(&boxcar_finish_kernel<NWT>),
             reinterpret_cast<const void*>(&boxcar_batch_kernel<NWT>), static_cast<int>(sizeof(BoxPart<NWT>))};
 }
@@ -745,7 +898,9 @@ hipError_t launch_boxcar(const BoxcarArgs& a_in, hipStream_t stream) {
     // kernel) the rows are not split.
     BoxSplit sp{nullptr, 1, 0};
     Scratch ws;
-    if (a.ndm > 0) sp = box_split(a.ndm, (a.nt + kBoxTile - 1) / kBoxTile, nwt);
+    const int ntiles = (a.nt + kBoxTile - 1) / kBoxTile;
+    const bool list = a.want_cands && a.ndm <= kListRows && ntiles <= kListTiles;
+    if (a.ndm > 0 && !list) sp = box_split(a.ndm, ntiles, nwt);
     if (sp.parts > 1) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
         int dev = -1;
@@ -780,7 +935,7 @@ hipError_t launch_boxcar(const BoxcarArgs& a_in, hipStream_t stream) {
     a.tmax_ok = lds > 0 ? 1 : 0;
     const int prof = prof_begin(TX_KERNEL_BOXCAR, stream);
     void* args[] = {&a};
-    hipError_t e = hipLaunchKernel(fn.row, dim3(a.ndm), dim3(kThreads), args, static_cast<size_t>(lds), stream);
+    hipError_t e = hipLaunchKernel(list ? fn.list : fn.row, dim3(a.ndm), dim3(kThreads), args, static_cast<size_t>(lds), stream);
     if (e == hipSuccess) e = hipGetLastError();
     prof_end(prof, stream);
     return e;
