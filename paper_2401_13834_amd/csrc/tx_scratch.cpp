@@ -30,6 +30,7 @@ struct Buf {
     hipStream_t last = nullptr;
     bool used = false;      // `done` has been recorded
     bool busy = false;      // a call holds it
+    bool lost = false;      // or held it, and it is not known when its kernels end
 };
 
 struct DevBufs {
@@ -116,11 +117,12 @@ hipError_t scratch_put(Scratch* s, hipStream_t stream) {
     *s = Scratch{};
     if (!b) return hipFreeAsync(p, stream);
     hipError_t e = hipEventRecord(b->done, stream);
-    if (e != hipSuccess) e = hipStreamSynchronize(stream);      // nothing to wait for later then
+    const bool recorded = e == hipSuccess;
+    if (!recorded) e = hipStreamSynchronize(stream);            // nothing to wait for later then
     std::lock_guard<std::mutex> lock(g_mu);
-    b->used = true;
+    b->used = recorded;
     b->last = stream;
-    b->busy = false;
+    b->busy = b->lost = e != hipSuccess;                        // (given up by the next trim)
     return e;
 }
 
@@ -129,7 +131,7 @@ void scratch_trim(int dev) {
     std::lock_guard<std::mutex> lock(g_mu);
     DevBufs& d = g_dev[dev];
     for (Buf& b : d.bufs) {
-        if (!b.p || b.busy) continue;
+        if (!b.p || (b.busy && !b.lost)) continue;
         d.bytes -= b.bytes;
         free_buf(&b);
     }

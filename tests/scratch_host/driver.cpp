@@ -1,0 +1,168 @@
+// The kept scratch (tx_scratch.cpp) over simulated streams, events and a card
+// of limited memory.  `driver NAME` runs one check and ends with 0 if it holds.
+#include <chrono>
+#include <condition_variable>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <mutex>
+#include <string>
+#include <thread>
+#include <vector>
+
+#include "../../paper_2401_13834_amd/csrc/tx_internal.h"
+
+struct Stream {
+    int queued = 0, done = 0;          // work items
+    bool capturing = false, record_fails = false, sync_fails = false;
+};
+struct Event {
+    Stream* s = nullptr;
+    int at = 0;                        // complete once s->done >= at
+};
+
+static std::recursive_mutex sim;
+static size_t memory_left = size_t(1) << 40;
+static std::map<void*, size_t> live;
+static int mallocs = 0, frees = 0, pool_mallocs = 0;
+static thread_local int device = 0;
+static thread_local hipError_t last_error = hipSuccess;
+static void (*in_malloc)() = nullptr;  // called from hipMalloc, with no lock held
+
+static hipError_t say(hipError_t e) {
+    if (e != hipSuccess) last_error = e;
+    return e;
+}
+static hipError_t get(void** p, size_t bytes) {
+    std::lock_guard<std::recursive_mutex> l(sim);
+    if (bytes > memory_left) return say(hipErrorOutOfMemory);
+    memory_left -= bytes;
+    *p = std::malloc(1);
+    live[*p] = bytes;
+    return hipSuccess;
+}
+static hipError_t put(void* p) {
+    std::lock_guard<std::recursive_mutex> l(sim);
+    if (!live.count(p)) return say(hipErrorInvalidValue);
+    memory_left += live[p];
+    live.erase(p);
+    return hipSuccess;                 // (the address is not given out again)
+}
+
+hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
+hipError_t hipMalloc(void** p, size_t bytes) {
+    if (in_malloc) in_malloc();
+    ++mallocs;
+    return get(p, bytes);
+}
+hipError_t hipFree(void* p) { ++frees; return put(p); }
+hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t) { ++pool_mallocs; return get(p, bytes); }
+hipError_t hipFreeAsync(void* p, hipStream_t) { return put(p); }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = new Event; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { delete e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    std::lock_guard<std::recursive_mutex> l(sim);
+    if (s->record_fails) return say(hipErrorUnknown);
+    e->s = s;
+    e->at = s->queued;
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) {
+    std::lock_guard<std::recursive_mutex> l(sim);
+    return !e->s || e->s->done >= e->at ? hipSuccess : say(hipErrorNotReady);
+}
+hipError_t hipEventSynchronize(hipEvent_t e) {
+    std::lock_guard<std::recursive_mutex> l(sim);
+    if (e->s && e->s->done < e->at) e->s->done = e->at;
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    std::lock_guard<std::recursive_mutex> l(sim);
+    if (s->sync_fails) return say(hipErrorUnknown);
+    s->done = s->queued;
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c) {
+    *c = s->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }
+
+#define CHECK(c)                                                            \
+    do {                                                                    \
+        if (!(c)) {                                                         \
+            std::fprintf(stderr, "line %d: %s\n", __LINE__, #c);            \
+            std::exit(1);                                                   \
+        }                                                                   \
+    } while (0)
+
+constexpr size_t MB = size_t(1) << 20;
+
+static tx::Scratch take(size_t bytes, Stream* s) {
+    tx::Scratch x;
+    CHECK(tx::scratch_get(bytes, s, &x) == hipSuccess);
+    CHECK(x.p);
+    ++s->queued;                       // the call's kernels
+    return x;
+}
+
+// Kept buffers are taken again: on the same stream at once, on another when
+// the work behind them is done; captures and large buffers use the pool.
+static void reuse() {
+    Stream a, b, c;
+    c.capturing = true;
+    tx::Scratch x = take(MB, &a);
+    void* p = x.p;
+    CHECK(x.kept);
+    CHECK(tx::scratch_put(&x, &a) == hipSuccess && !x.p);
+    tx::Scratch y = take(3 * MB, &b);  // a's work has not ended
+    CHECK(y.p != p);
+    CHECK(tx::scratch_put(&y, &b) == hipSuccess);
+    x = take(4 * MB, &a);
+    CHECK(x.p == p);
+    CHECK(tx::scratch_put(&x, &a) == hipSuccess);
+    a.done = a.queued;
+    b.done = b.queued;
+    x = take(MB, &b);
+    y = take(MB, &a);
+    CHECK(mallocs == 2 && x.p != y.p);
+    CHECK(tx::scratch_put(&x, &b) == hipSuccess && tx::scratch_put(&y, &a) == hipSuccess);
+    for (Stream* s : {&a, &c}) {
+        x = take(s == &c ? MB : 65 * MB, s);
+        CHECK(!x.kept);
+        CHECK(tx::scratch_put(&x, s) == hipSuccess);
+    }
+    CHECK(pool_mallocs == 2);
+    tx::scratch_trim(0);
+    CHECK(frees == 2 && live.empty());
+}
+
+// A buffer whose last work is unknown (neither the event nor the wait worked)
+// is not handed out again before a trim, which follows a device synchronisation.
+static void lost() {
+    Stream a, b;
+    tx::Scratch x = take(MB, &a);
+    void* p = x.p;
+    a.record_fails = a.sync_fails = true;
+    CHECK(tx::scratch_put(&x, &a) != hipSuccess);
+    for (Stream* s : {&b, &a}) {
+        tx::Scratch y = take(MB, s);
+        CHECK(y.p != p);
+        s->record_fails = s->sync_fails = false;
+        CHECK(tx::scratch_put(&y, s) == hipSuccess);
+        s->done = s->queued;
+    }
+    tx::scratch_trim(0);
+    CHECK(live.empty());
+}
+
+int main(int argc, char** argv) {
+    const std::map<std::string, void (*)()> checks = {{"reuse", reuse}, {"lost", lost}};
+    const auto it = checks.find(argc > 1 ? argv[1] : "");
+    if (it == checks.end()) return 2;
+    it->second();
+    return 0;
+}

@@ -1,0 +1,38 @@
+// The few HIP runtime calls that the kept scratch makes, simulated on the host
+// for test_scratch_cpu.py (driver.cpp defines them).
+#pragma once
+#include <cstddef>
+#include <cstdint>
+
+struct Stream;
+struct Event;
+struct Pool;
+typedef Stream* hipStream_t;
+typedef Event* hipEvent_t;
+typedef Pool* hipMemPool_t;
+enum hipError_t {
+    hipSuccess = 0,
+    hipErrorInvalidValue = 1,
+    hipErrorOutOfMemory = 2,
+    hipErrorNotReady = 600,
+    hipErrorUnknown = 999
+};
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone, hipStreamCaptureStatusActive };
+enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal, hipStreamCaptureModeRelaxed };
+constexpr unsigned hipEventDisableTiming = 2;
+
+hipError_t hipGetDevice(int* dev);
+hipError_t hipGetLastError();
+hipError_t hipMalloc(void** p, size_t bytes);
+hipError_t hipFree(void* p);
+hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t s);
+hipError_t hipFreeAsync(void* p, hipStream_t s);
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned flags);
+hipError_t hipEventDestroy(hipEvent_t e);
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s);
+hipError_t hipEventQuery(hipEvent_t e);
+hipError_t hipEventSynchronize(hipEvent_t e);
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
+hipError_t hipStreamSynchronize(hipStream_t s);
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status);
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* mode);
