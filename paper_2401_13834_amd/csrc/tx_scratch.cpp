@@ -10,7 +10,8 @@
 // behind the last user's kernels has completed.  Larger buffers, captures and calls that
 // find neither a free buffer nor room for another use the stream-ordered pool
 // as before.  Per device at most kMaxBufs buffers and kMaxBytes bytes are
-// kept; tx_pool_trim gives them back.
+// kept; tx_pool_trim gives them back, and so does a call for which the pool has
+// no memory left.
 #include <mutex>
 
 #include "tx_internal.h"
@@ -90,14 +91,31 @@ Buf* take(DevBufs& d, size_t bytes, hipStream_t stream) {
     return best;
 }
 
+// Frees the buffers that no call holds, once their last kernels have ended.
+// False if there were none.
+bool give_up_idle(int dev) {
+    RelaxedCapture relaxed;
+    std::lock_guard<std::mutex> lock(g_mu);
+    DevBufs& d = g_dev[dev];
+    bool any = false;
+    for (Buf& b : d.bufs) {
+        if (!b.p || b.busy || (b.used && hipEventSynchronize(b.done) != hipSuccess)) continue;
+        d.bytes -= b.bytes;
+        free_buf(&b);
+        any = true;
+    }
+    return any;
+}
+
 }  // namespace
 
 hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out) {
     *out = Scratch{};
     int dev = -1;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
-    if (bytes <= kMaxBuf && hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-        hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) {
+    const bool keeps = hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+                       hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices;
+    if (keeps && bytes <= kMaxBuf) {
         RelaxedCapture relaxed;
         std::lock_guard<std::mutex> lock(g_mu);
         if (Buf* b = take(g_dev[dev], bytes, stream)) {
@@ -107,7 +125,13 @@ hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out) {
     }
     (void)hipGetLastError();                         // (an event that has not completed is no error)
     if (out->p) return hipSuccess;
-    return hipMallocAsync(&out->p, bytes > 0 ? bytes : 1, stream);
+    hipError_t e = hipMallocAsync(&out->p, bytes > 0 ? bytes : 1, stream);
+    if (e == hipErrorOutOfMemory && keeps && give_up_idle(dev)) {
+        (void)hipGetLastError();
+        e = hipMallocAsync(&out->p, bytes > 0 ? bytes : 1, stream);
+    }
+    if (e != hipSuccess) out->p = nullptr;
+    return e;
 }
 
 hipError_t scratch_put(Scratch* s, hipStream_t stream) {

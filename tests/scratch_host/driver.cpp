@@ -159,8 +159,28 @@ static void lost() {
     CHECK(live.empty());
 }
 
+// A call that the card has no room for beside the kept buffers gets theirs, once
+// the work in them is done; buffers in use stay.
+static void memory() {
+    Stream a, b;
+    tx::Scratch x = take(64 * MB, &a), y = take(MB, &a);
+    CHECK(tx::scratch_put(&x, &a) == hipSuccess);
+    memory_left = 50 * MB;
+    x = take(100 * MB, &b);
+    CHECK(!x.kept && a.done == 2);
+    CHECK(live.size() == 2 && live.count(y.p));
+    tx::Scratch z;
+    CHECK(tx::scratch_get(100 * MB, &b, &z) == hipErrorOutOfMemory && !z.p);
+    CHECK(tx::scratch_put(&z, &b) == hipSuccess);
+    CHECK(tx::scratch_put(&x, &b) == hipSuccess && tx::scratch_put(&y, &a) == hipSuccess);
+    a.capturing = true;                // a capture touches nothing that is kept
+    CHECK(tx::scratch_get(200 * MB, &a, &z) == hipErrorOutOfMemory && live.size() == 1);
+    tx::scratch_trim(0);
+    CHECK(live.empty());
+}
+
 int main(int argc, char** argv) {
-    const std::map<std::string, void (*)()> checks = {{"reuse", reuse}, {"lost", lost}};
+    const std::map<std::string, void (*)()> checks = {{"reuse", reuse}, {"lost", lost}, {"memory", memory}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     if (it == checks.end()) return 2;
     it->second();
