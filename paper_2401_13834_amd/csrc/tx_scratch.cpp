@@ -7,11 +7,13 @@
 // kernels of a small block take.  Here a buffer of up to kMaxBuf bytes stays
 // allocated after the call and is taken again by a later one: by a call on the
 // same stream, which its kernels follow, or by any once the event recorded
-// behind the last user's kernels has completed.  Larger buffers, captures and calls that
-// find neither a free buffer nor room for another use the stream-ordered pool
-// as before.  Per device at most kMaxBufs buffers and kMaxBytes bytes are
-// kept; tx_pool_trim gives them back, and so does a call for which the pool has
-// no memory left.
+// behind the last user's kernels has completed.  Per device at most kMaxBufs
+// buffers and kMaxBytes bytes are kept: where a new one finds no room, the
+// smallest idle ones (all too small for the call) make way, so buffers only grow and
+// this ends.  Larger requests, captures and calls that still find no room use
+// the stream-ordered pool.  tx_pool_trim gives the buffers back, and so does a call
+// for which the pool has no memory left.
+#include <algorithm>
 #include <mutex>
 
 #include "tx_internal.h"
@@ -57,16 +59,32 @@ void free_buf(Buf* b) {
     *b = Buf{};
 }
 
+// A slot for a buffer of `size` bytes, within the limits, in the place of the
+// smallest idle buffers where none is free; null if those would not do.  Called
+// with g_mu held.
+Buf* make_room(DevBufs& d, size_t size) {
+    Buf* idle[kMaxBufs];
+    int n = 0;
+    Buf* empty = nullptr;
+    for (Buf& b : d.bufs) {
+        if (!b.p) empty = &b;
+        else if (!b.busy && b.bytes < size && (!b.used || hipEventQuery(b.done) == hipSuccess)) idle[n++] = &b;
+    }
+    std::sort(idle, idle + n, [](const Buf* x, const Buf* y) { return x->bytes < y->bytes; });
+    size_t left = d.bytes;
+    int k = 0;
+    while ((left + size > kMaxBytes || (!empty && k == 0)) && k < n) left -= idle[k++]->bytes;
+    if (left + size > kMaxBytes || (!empty && k == 0)) return nullptr;
+    for (int i = 0; i < k; ++i) free_buf(idle[i]);
+    d.bytes = left;
+    return empty ? empty : idle[0];
+}
+
 // A kept buffer of at least `bytes` for `stream`, or null.  Called with g_mu held.
 Buf* take(DevBufs& d, size_t bytes, hipStream_t stream) {
     Buf* best = nullptr;
-    Buf* empty = nullptr;
     for (Buf& b : d.bufs) {                          // the smallest that is ready
-        if (!b.p) {
-            empty = &b;
-            continue;
-        }
-        if (b.busy || b.bytes < bytes || (best && b.bytes >= best->bytes)) continue;
+        if (!b.p || b.busy || b.bytes < bytes || (best && b.bytes >= best->bytes)) continue;
         if (b.used && b.last != stream && hipEventQuery(b.done) != hipSuccess) continue;
         best = &b;
     }
@@ -75,9 +93,11 @@ Buf* take(DevBufs& d, size_t bytes, hipStream_t stream) {
     if (best && best->used && best->last == stream && hipStreamWaitEvent(stream, best->done, 0) != hipSuccess)
         best = nullptr;
     if (!best) {
+        Buf* empty = nullptr;
         size_t size = kMinBuf;
         while (size < bytes) size *= 2;
-        if (!empty || d.bytes + size > kMaxBytes) return nullptr;
+        empty = make_room(d, size);
+        if (!empty) return nullptr;
         if (hipMalloc(&empty->p, size) != hipSuccess ||
             hipEventCreateWithFlags(&empty->done, hipEventDisableTiming) != hipSuccess) {
             free_buf(empty);

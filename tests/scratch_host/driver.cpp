@@ -179,8 +179,54 @@ static void memory() {
     CHECK(live.empty());
 }
 
+static void fill(std::vector<tx::Scratch>* x, int n, size_t bytes, Stream* s) {
+    for (int i = 0; i < n; ++i) x->push_back(take(bytes, s));
+}
+
+static void empty(std::vector<tx::Scratch>* x, Stream* s) {
+    for (tx::Scratch& y : *x) CHECK(tx::scratch_put(&y, s) == hipSuccess);
+    x->clear();
+}
+
+// No slot (16 buffers) or no room (512 MB) left: the smallest idle buffers make
+// way for a larger one; pending ones and those in use do not.
+static void room() {
+    Stream a, b;
+    std::vector<tx::Scratch> x, y;
+    fill(&x, 16, MB, &a);
+    empty(&x, &a);
+    x.push_back(take(5 * MB, &b));     // a's work has not ended
+    CHECK(!x[0].kept);
+    empty(&x, &b);
+    a.done = a.queued;
+    x.push_back(take(5 * MB, &b));
+    CHECK(x[0].kept && frees == 1 && live.size() == 16);
+    empty(&x, &b);
+    b.done = b.queued;
+    fill(&y, 7, 64 * MB, &b);          // 448 MB in use, and 8 small ones and the 8 MB one idle
+    CHECK(frees == 8);
+    for (const tx::Scratch& s : y) CHECK(s.kept);
+    x.push_back(take(33 * MB, &a));    // 64 MB: all the small ones go
+    CHECK(x[0].kept && live.size() == 8);
+    x.push_back(take(MB, &a));         // nothing idle is left
+    CHECK(!x[1].kept);
+    empty(&x, &a);
+    empty(&y, &b);
+    a.done = a.queued;
+    b.done = b.queued;
+    const int before = mallocs;
+    for (size_t m : {1, 60, 5, 33, 64}) {
+        x.push_back(take(m * MB, &a));
+        CHECK(x[0].kept);
+        empty(&x, &a);
+    }
+    CHECK(mallocs == before);          // (nothing grows any more)
+    tx::scratch_trim(0);
+    CHECK(live.empty());
+}
+
 int main(int argc, char** argv) {
-    const std::map<std::string, void (*)()> checks = {{"reuse", reuse}, {"lost", lost}, {"memory", memory}};
+    const std::map<std::string, void (*)()> checks = {{"reuse", reuse}, {"lost", lost}, {"memory", memory}, {"room", room}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     if (it == checks.end()) return 2;
     it->second();
