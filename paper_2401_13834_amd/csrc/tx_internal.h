@@ -375,7 +375,8 @@ tx_status retain_pool(int dev);
 // retain_pool).  scratch_put, after the last kernel, gives it back.
 struct Scratch {
     void* p = nullptr;
-    void* kept = nullptr;
+    void* kept = nullptr;   // tx_scratch.cpp's: the kept buffer and its device
+    void* dev = nullptr;
 };
 hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out);
 hipError_t scratch_put(Scratch* s, hipStream_t stream);

@@ -36,13 +36,16 @@ struct Buf {
     bool lost = false;      // or held it, and it is not known when its kernels end
 };
 
+// The lock is held to look and to mark only, never across a call that allocates,
+// frees or waits: a slot that is being filled is marked busy, and buffers to be freed are
+// taken out of the list first.
 struct DevBufs {
+    std::mutex mu;
     Buf bufs[kMaxBufs];     // p null: no buffer
-    size_t bytes = 0;
+    size_t bytes = 0;       // (with those of slots being filled)
 };
 
 constexpr int kMaxDevices = 64;
-std::mutex g_mu;
 DevBufs g_dev[kMaxDevices];
 
 // Calls that a capture elsewhere in the process forbids are allowed for the
@@ -53,38 +56,29 @@ struct RelaxedCapture {
     ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
-void free_buf(Buf* b) {
-    if (b->p) (void)hipFree(b->p);
-    if (b->done) (void)hipEventDestroy(b->done);
-    *b = Buf{};
-}
-
-// A slot for a buffer of `size` bytes, within the limits, in the place of the
-// smallest idle buffers where none is free; null if those would not do.  Called
-// with g_mu held.
-Buf* make_room(DevBufs& d, size_t size) {
-    Buf* idle[kMaxBufs];
+// Buffers taken out of the list.
+struct Freed {
+    Buf bufs[kMaxBufs];
     int n = 0;
-    Buf* empty = nullptr;
-    for (Buf& b : d.bufs) {
-        if (!b.p) empty = &b;
-        else if (!b.busy && b.bytes < size && (!b.used || hipEventQuery(b.done) == hipSuccess)) idle[n++] = &b;
+    void take(DevBufs& d, Buf* b) {                  // with the lock held
+        bufs[n++] = *b;
+        d.bytes -= b->bytes;
+        *b = Buf{};
     }
-    std::sort(idle, idle + n, [](const Buf* x, const Buf* y) { return x->bytes < y->bytes; });
-    size_t left = d.bytes;
-    int k = 0;
-    while ((left + size > kMaxBytes || (!empty && k == 0)) && k < n) left -= idle[k++]->bytes;
-    if (left + size > kMaxBytes || (!empty && k == 0)) return nullptr;
-    for (int i = 0; i < k; ++i) free_buf(idle[i]);
-    d.bytes = left;
-    return empty ? empty : idle[0];
-}
+    ~Freed() {                                       // without
+        for (int i = 0; i < n; ++i) {
+            if (bufs[i].used) (void)hipEventSynchronize(bufs[i].done);
+            (void)hipFree(bufs[i].p);
+            (void)hipEventDestroy(bufs[i].done);
+        }
+    }
+};
 
-// A kept buffer of at least `bytes` for `stream`, or null.  Called with g_mu held.
-Buf* take(DevBufs& d, size_t bytes, hipStream_t stream) {
+// The smallest kept buffer of at least `bytes` that is ready for `stream`, or null.
+Buf* ready(DevBufs& d, size_t bytes, hipStream_t stream) {
     Buf* best = nullptr;
-    for (Buf& b : d.bufs) {                          // the smallest that is ready
-        if (!b.p || b.busy || b.bytes < bytes || (best && b.bytes >= best->bytes)) continue;
+    for (Buf& b : d.bufs) {
+        if (b.busy || !b.p || b.bytes < bytes || (best && b.bytes >= best->bytes)) continue;
         if (b.used && b.last != stream && hipEventQuery(b.done) != hipSuccess) continue;
         best = &b;
     }
@@ -92,39 +86,72 @@ Buf* take(DevBufs& d, size_t bytes, hipStream_t stream) {
     // waits for the event; on the stream that recorded it that is nothing.)
     if (best && best->used && best->last == stream && hipStreamWaitEvent(stream, best->done, 0) != hipSuccess)
         best = nullptr;
-    if (!best) {
-        Buf* empty = nullptr;
-        size_t size = kMinBuf;
-        while (size < bytes) size *= 2;
-        empty = make_room(d, size);
-        if (!empty) return nullptr;
-        if (hipMalloc(&empty->p, size) != hipSuccess ||
-            hipEventCreateWithFlags(&empty->done, hipEventDisableTiming) != hipSuccess) {
-            free_buf(empty);
-            return nullptr;
-        }
-        empty->bytes = size;
-        d.bytes += size;
-        best = empty;
-    }
-    best->busy = true;
+    if (best) best->busy = true;
     return best;
+}
+
+// A busy slot for a new buffer of `size` bytes, within the limits, in the place
+// of the smallest idle buffers where none is free; null if those would not do.
+Buf* make_room(DevBufs& d, size_t size, Freed* old) {
+    Buf* idle[kMaxBufs];
+    int n = 0;
+    Buf* empty = nullptr;
+    for (Buf& b : d.bufs) {
+        if (b.busy) continue;
+        if (!b.p) empty = &b;
+        else if (b.bytes < size && (!b.used || hipEventQuery(b.done) == hipSuccess)) idle[n++] = &b;
+    }
+    std::sort(idle, idle + n, [](const Buf* x, const Buf* y) { return x->bytes < y->bytes; });
+    size_t left = d.bytes;
+    int k = 0;
+    while ((left + size > kMaxBytes || (!empty && k == 0)) && k < n) left -= idle[k++]->bytes;
+    if (left + size > kMaxBytes || (!empty && k == 0)) return nullptr;
+    for (int i = 0; i < k; ++i) old->take(d, idle[i]);
+    if (!empty) empty = idle[0];
+    empty->busy = true;
+    empty->bytes = size;
+    d.bytes += size;
+    return empty;
+}
+
+// A kept or new buffer of at least `bytes` for `stream`, or null.
+Buf* take(DevBufs& d, size_t bytes, hipStream_t stream) {
+    size_t size = kMinBuf;
+    while (size < bytes) size *= 2;
+    Buf* b;
+    {
+        Freed old;
+        std::lock_guard<std::mutex> lock(d.mu);
+        b = ready(d, bytes, stream);
+        if (b) return b;
+        b = make_room(d, size, &old);
+        if (!b) return nullptr;
+    }
+    void* p = nullptr;
+    hipEvent_t done = nullptr;
+    const bool ok = hipMalloc(&p, size) == hipSuccess &&
+                    hipEventCreateWithFlags(&done, hipEventDisableTiming) == hipSuccess;
+    if (!ok && p) (void)hipFree(p);
+    std::lock_guard<std::mutex> lock(d.mu);
+    if (!ok) {
+        d.bytes -= size;
+        *b = Buf{};
+        return nullptr;
+    }
+    b->p = p;
+    b->done = done;
+    return b;
 }
 
 // Frees the buffers that no call holds, once their last kernels have ended.
 // False if there were none.
-bool give_up_idle(int dev) {
+bool give_up_idle(DevBufs& d) {
     RelaxedCapture relaxed;
-    std::lock_guard<std::mutex> lock(g_mu);
-    DevBufs& d = g_dev[dev];
-    bool any = false;
-    for (Buf& b : d.bufs) {
-        if (!b.p || b.busy || (b.used && hipEventSynchronize(b.done) != hipSuccess)) continue;
-        d.bytes -= b.bytes;
-        free_buf(&b);
-        any = true;
-    }
-    return any;
+    Freed old;
+    std::lock_guard<std::mutex> lock(d.mu);
+    for (Buf& b : d.bufs)
+        if (b.p && !b.busy) old.take(d, &b);
+    return old.n > 0;
 }
 
 }  // namespace
@@ -137,16 +164,16 @@ hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out) {
                        hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices;
     if (keeps && bytes <= kMaxBuf) {
         RelaxedCapture relaxed;
-        std::lock_guard<std::mutex> lock(g_mu);
         if (Buf* b = take(g_dev[dev], bytes, stream)) {
             out->p = b->p;
             out->kept = b;
+            out->dev = &g_dev[dev];
         }
     }
     (void)hipGetLastError();                         // (an event that has not completed is no error)
     if (out->p) return hipSuccess;
     hipError_t e = hipMallocAsync(&out->p, bytes > 0 ? bytes : 1, stream);
-    if (e == hipErrorOutOfMemory && keeps && give_up_idle(dev)) {
+    if (e == hipErrorOutOfMemory && keeps && give_up_idle(g_dev[dev])) {
         (void)hipGetLastError();
         e = hipMallocAsync(&out->p, bytes > 0 ? bytes : 1, stream);
     }
@@ -157,13 +184,14 @@ hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out) {
 hipError_t scratch_put(Scratch* s, hipStream_t stream) {
     if (!s->p) return hipSuccess;
     Buf* b = static_cast<Buf*>(s->kept);
+    DevBufs* d = static_cast<DevBufs*>(s->dev);
     void* p = s->p;
     *s = Scratch{};
     if (!b) return hipFreeAsync(p, stream);
     hipError_t e = hipEventRecord(b->done, stream);
     const bool recorded = e == hipSuccess;
     if (!recorded) e = hipStreamSynchronize(stream);            // nothing to wait for later then
-    std::lock_guard<std::mutex> lock(g_mu);
+    std::lock_guard<std::mutex> lock(d->mu);
     b->used = recorded;
     b->last = stream;
     b->busy = b->lost = e != hipSuccess;                        // (given up by the next trim)
@@ -172,13 +200,11 @@ hipError_t scratch_put(Scratch* s, hipStream_t stream) {
 
 void scratch_trim(int dev) {
     if (dev < 0 || dev >= kMaxDevices) return;
-    std::lock_guard<std::mutex> lock(g_mu);
     DevBufs& d = g_dev[dev];
-    for (Buf& b : d.bufs) {
-        if (!b.p || (b.busy && !b.lost)) continue;
-        d.bytes -= b.bytes;
-        free_buf(&b);
-    }
+    Freed old;
+    std::lock_guard<std::mutex> lock(d.mu);
+    for (Buf& b : d.bufs)
+        if (b.p && (!b.busy || b.lost)) old.take(d, &b);
 }
 
 }  // namespace tx

@@ -28,7 +28,8 @@ static std::map<void*, size_t> live;
 static int mallocs = 0, frees = 0, pool_mallocs = 0;
 static thread_local int device = 0;
 static thread_local hipError_t last_error = hipSuccess;
-static void (*in_malloc)() = nullptr;  // called from hipMalloc, with no lock held
+static void (*in_malloc)() = nullptr;  // called from hipMalloc and hipFree
+static void (*in_free)() = nullptr;
 
 static hipError_t say(hipError_t e) {
     if (e != hipSuccess) last_error = e;
@@ -57,7 +58,11 @@ hipError_t hipMalloc(void** p, size_t bytes) {
     ++mallocs;
     return get(p, bytes);
 }
-hipError_t hipFree(void* p) { ++frees; return put(p); }
+hipError_t hipFree(void* p) {
+    if (in_free) in_free();
+    ++frees;
+    return put(p);
+}
 hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t) { ++pool_mallocs; return get(p, bytes); }
 hipError_t hipFreeAsync(void* p, hipStream_t) { return put(p); }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = new Event; return hipSuccess; }
@@ -225,8 +230,60 @@ static void room() {
     CHECK(live.empty());
 }
 
+// While one thread allocates or frees, another takes and gives back kept buffers
+// of the same device and of another one.
+static std::mutex step_mu;
+static std::condition_variable step_cv;
+static int step = 0;                   // 1: a thread is inside the runtime, 2: the other one is done
+
+static bool wait_step(int n) {
+    std::unique_lock<std::mutex> l(step_mu);
+    return step_cv.wait_for(l, std::chrono::seconds(5), [&] { return step >= n; });
+}
+static void set_step(int n) {
+    std::lock_guard<std::mutex> l(step_mu);
+    step = n;
+    step_cv.notify_all();
+}
+static void inside() {
+    set_step(1);
+    CHECK(wait_step(2));               // a lock held here keeps the other thread out
+}
+
+static void locks() {
+    Stream s[2], big;
+    for (int d = 0; d < 2; ++d) {
+        device = d;
+        tx::Scratch x = take(MB, &s[d]);
+        CHECK(tx::scratch_put(&x, &s[d]) == hipSuccess);
+    }
+    device = 0;
+    for (int k = 0; k < 2; ++k) {
+        step = 0;
+        (k == 0 ? in_malloc : in_free) = inside;
+        std::thread t([&] {
+            if (k == 0) {
+                tx::Scratch x = take(60 * MB, &big);
+                CHECK(x.kept && tx::scratch_put(&x, &big) == hipSuccess);
+            } else {
+                device = 1;
+                tx::scratch_trim(1);
+            }
+        });
+        CHECK(wait_step(1));
+        for (int d = 0; d < 2 - k; ++d) {
+            device = d;
+            tx::Scratch x = take(MB, &s[d]);
+            CHECK(x.kept && tx::scratch_put(&x, &s[d]) == hipSuccess);
+        }
+        set_step(2);
+        t.join();
+        in_malloc = in_free = nullptr;
+    }
+}
+
 int main(int argc, char** argv) {
-    const std::map<std::string, void (*)()> checks = {{"reuse", reuse}, {"lost", lost}, {"memory", memory}, {"room", room}};
+    const std::map<std::string, void (*)()> checks = {{"reuse", reuse}, {"lost", lost}, {"memory", memory}, {"room", room}, {"locks", locks}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     if (it == checks.end()) return 2;
     it->second();
