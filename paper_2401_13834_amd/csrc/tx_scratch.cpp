@@ -158,6 +158,7 @@ bool give_up_idle(DevBufs& d) {
 
 hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out) {
     *out = Scratch{};
+    const bool clean = hipPeekAtLastError() == hipSuccess;   // else an error from before is left for its reader
     int dev = -1;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
     const bool keeps = hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
@@ -170,11 +171,11 @@ hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out) {
             out->dev = &g_dev[dev];
         }
     }
-    (void)hipGetLastError();                         // (an event that has not completed is no error)
+    if (clean) (void)hipGetLastError();              // (an event that has not completed is no error)
     if (out->p) return hipSuccess;
     hipError_t e = hipMallocAsync(&out->p, bytes > 0 ? bytes : 1, stream);
     if (e == hipErrorOutOfMemory && keeps && give_up_idle(g_dev[dev])) {
-        (void)hipGetLastError();
+        if (clean) (void)hipGetLastError();
         e = hipMallocAsync(&out->p, bytes > 0 ? bytes : 1, stream);
     }
     if (e != hipSuccess) out->p = nullptr;

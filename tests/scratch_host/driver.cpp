@@ -53,6 +53,7 @@ static hipError_t put(void* p) {
 
 hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
 hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
+hipError_t hipPeekAtLastError() { return last_error; }
 hipError_t hipMalloc(void** p, size_t bytes) {
     if (in_malloc) in_malloc();
     ++mallocs;
@@ -282,8 +283,23 @@ static void locks() {
     }
 }
 
+// Errors from before a call stay for their reader; the call's own (an event that
+// has not completed) do not come up later.
+static void error() {
+    Stream a, b;
+    tx::Scratch x = take(MB, &a);
+    CHECK(tx::scratch_put(&x, &a) == hipSuccess);
+    x = take(MB, &b);
+    CHECK(hipGetLastError() == hipSuccess);
+    CHECK(tx::scratch_put(&x, &b) == hipSuccess);
+    last_error = hipErrorInvalidValue;
+    x = take(MB, &a);
+    CHECK(tx::scratch_put(&x, &a) == hipSuccess);
+    CHECK(hipGetLastError() == hipErrorInvalidValue);
+}
+
 int main(int argc, char** argv) {
-    const std::map<std::string, void (*)()> checks = {{"reuse", reuse}, {"lost", lost}, {"memory", memory}, {"room", room}, {"locks", locks}};
+    const std::map<std::string, void (*)()> checks = {{"reuse", reuse}, {"lost", lost}, {"memory", memory}, {"room", room}, {"locks", locks}, {"error", error}};
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     if (it == checks.end()) return 2;
     it->second();

@@ -23,6 +23,7 @@ constexpr unsigned hipEventDisableTiming = 2;
 
 hipError_t hipGetDevice(int* dev);
 hipError_t hipGetLastError();
+hipError_t hipPeekAtLastError();
 hipError_t hipMalloc(void** p, size_t bytes);
 hipError_t hipFree(void* p);
 hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t s);

@@ -24,7 +24,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["reuse", "lost", "memory", "room", "locks"])
+@pytest.mark.parametrize("check", ["reuse", "lost", "memory", "room", "locks", "error"])
 def test_kept_scratch(driver, check):
     r = subprocess.run([driver, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stderr
