@@ -74,12 +74,16 @@ struct Freed {
     }
 };
 
+// Whether the kernels of the buffer's last user have ended.  Not asked while an
+// error of the caller's is unread (`ask` false), which "not ready" would replace.
+bool ended(const Buf& b, bool ask) { return !b.used || (ask && hipEventQuery(b.done) == hipSuccess); }
+
 // The smallest kept buffer of at least `bytes` that is ready for `stream`, or null.
-Buf* ready(DevBufs& d, size_t bytes, hipStream_t stream) {
+Buf* ready(DevBufs& d, size_t bytes, hipStream_t stream, bool ask) {
     Buf* best = nullptr;
     for (Buf& b : d.bufs) {
         if (b.busy || !b.p || b.bytes < bytes || (best && b.bytes >= best->bytes)) continue;
-        if (b.used && b.last != stream && hipEventQuery(b.done) != hipSuccess) continue;
+        if (b.last != stream && !ended(b, ask)) continue;
         best = &b;
     }
     // (The handle may be another stream's by now, so also the same handle
@@ -92,14 +96,14 @@ Buf* ready(DevBufs& d, size_t bytes, hipStream_t stream) {
 
 // A busy slot for a new buffer of `size` bytes, within the limits, in the place
 // of the smallest idle buffers where none is free; null if those would not do.
-Buf* make_room(DevBufs& d, size_t size, Freed* old) {
+Buf* make_room(DevBufs& d, size_t size, bool ask, Freed* old) {
     Buf* idle[kMaxBufs];
     int n = 0;
     Buf* empty = nullptr;
     for (Buf& b : d.bufs) {
         if (b.busy) continue;
         if (!b.p) empty = &b;
-        else if (b.bytes < size && (!b.used || hipEventQuery(b.done) == hipSuccess)) idle[n++] = &b;
+        else if (b.bytes < size && ended(b, ask)) idle[n++] = &b;
     }
     std::sort(idle, idle + n, [](const Buf* x, const Buf* y) { return x->bytes < y->bytes; });
     size_t left = d.bytes;
@@ -115,16 +119,16 @@ Buf* make_room(DevBufs& d, size_t size, Freed* old) {
 }
 
 // A kept or new buffer of at least `bytes` for `stream`, or null.
-Buf* take(DevBufs& d, size_t bytes, hipStream_t stream) {
+Buf* take(DevBufs& d, size_t bytes, hipStream_t stream, bool ask) {
     size_t size = kMinBuf;
     while (size < bytes) size *= 2;
     Buf* b;
     {
         Freed old;
         std::lock_guard<std::mutex> lock(d.mu);
-        b = ready(d, bytes, stream);
+        b = ready(d, bytes, stream, ask);
         if (b) return b;
-        b = make_room(d, size, &old);
+        b = make_room(d, size, ask, &old);
         if (!b) return nullptr;
     }
     void* p = nullptr;
@@ -165,7 +169,7 @@ hipError_t scratch_get(size_t bytes, hipStream_t stream, Scratch* out) {
                        hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices;
     if (keeps && bytes <= kMaxBuf) {
         RelaxedCapture relaxed;
-        if (Buf* b = take(g_dev[dev], bytes, stream)) {
+        if (Buf* b = take(g_dev[dev], bytes, stream, clean)) {
             out->p = b->p;
             out->kept = b;
             out->dev = &g_dev[dev];
