@@ -672,7 +672,8 @@ static int stage1_need(const tx_plan_s* p, const Stage1Variant& v) {
 }
 
 // Sizes that the matrix-core form holds: shifts in 15 bits, times in 32, the
-// rows of 4 trials within a buffer resource, its staged rows in LDS.
+// rows of 4 trials within a buffer resource (with 64 sub-bands, blocks of up to
+// 4.1M samples), its staged rows in LDS.
 static bool mx_fits(const tx_plan_s* p, int64_t nt) {
     return p->mx.spread < 16384 && nt + p->overlap + 2 * p->max_extent + 65536 < INT32_MAX &&
            8 * p->nsub * (nt + p->max_extent + 65536) < INT32_MAX && stage1_need(p, kS1[kDefaultMx]) <= device_max_lds();
@@ -690,8 +691,8 @@ static bool mx_fits(const tx_plan_s* p, int64_t nt) {
 // 1.03-2.3; at 2.25 (256 channels in 16 sub-bands, 2726 trials) 0.85, yet calls
 // one after the other took 447 us against 435, since the general form runs at
 // higher clocks.  Fewer trials (10 / m), 1.3-3.3 0.32-0.96 (one of 20 1.07),
-// above 0.83-2.25 (mean 1.3).  The plan alone decides, so that scratch sized
-// for a long block serves shorter ones.
+// above 0.83-2.25 (mean 1.3).  The block's length decides only where the form
+// no longer holds it (mx_fits): scratch sized for a long block serves shorter ones.
 static bool mx_pays(const tx_plan_s* p) {
     const double padded = static_cast<double>((p->ngroups + 15) / 16 * 16) / p->ngroups;
     if (p->ngroups < 100) return (p->mx.windows + 10.0 / p->m) * padded < 3.3;
@@ -703,10 +704,13 @@ bool default_stage1(const Tiles& t) { return t.s1 < 0 || t.s1 >= kNS1; }
 DedispGeom dedisp_geometry(const tx_plan_s* p, int64_t nt, const Tiles& want) {
     DedispGeom g{};
     g.tiles = want;
+    bool mx_below = false;           // the general form, but shorter blocks of the plan take the matrix-core form
     if (default_stage1(g.tiles)) {
         // (a plan that the general form refuses stays refused)
         const bool general = stage1_need(p, kS1[kDefaultS1]) <= device_max_lds();
-        g.tiles.s1 = general && mx_fits(p, nt) && mx_pays(p) ? kDefaultMx : kDefaultS1;
+        const bool pays = general && mx_pays(p);
+        g.tiles.s1 = pays && mx_fits(p, nt) ? kDefaultMx : kDefaultS1;
+        mx_below = pays && g.tiles.s1 == kDefaultS1 && mx_fits(p, 1);
     }
     if (g.tiles.s2 < 0 || g.tiles.s2 >= kNS2) g.tiles.s2 = kDefaultS2;
     const Stage1Variant v1 = kS1[g.tiles.s1];
@@ -739,19 +743,22 @@ DedispGeom dedisp_geometry(const tx_plan_s* p, int64_t nt, const Tiles& want) {
     // holds one 16-byte piece more than the W dwords the trials read), start
     // <= last tile start + max extent.
     const int64_t need = static_cast<int64_t>(std::max(g.n_ttiles2 - 1, 0)) * g.tt2 + p->max_extent + 2 * W2 + 8;
+    const int64_t len_mx = round_up(nt + p->max_extent + 15, 16);
+    const int64_t pitch_mx = round_up(std::max<int64_t>(need + 15, len_mx), 16);
     if (v1.mx) {
         // Series start up to 15 elements early; tiles are cut at multiples of
         // their length of v = u + D(c_j, f_s), which a sub-band's trials
         // start at different points of.
-        g.len1 = round_up(nt + p->max_extent + 15, 16);
-        g.B_pitch = round_up(std::max<int64_t>(need + 15, g.len1), 16);
+        g.len1 = len_mx;
+        g.B_pitch = pitch_mx;
         const auto tiles = [&](double spread) { return static_cast<int64_t>((g.len1 + spread + 15) / g.tt1) + 2; };
         const int64_t all = tiles(p->mx.vspread) * p->nsub * ((p->ngroups + g.J1 - 1) / g.J1);   // about
         g.run1 = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(all / kMxMinRuns, 8)));
         g.n_ttiles1 = static_cast<int32_t>((tiles(p->mx.vspread_max) + g.run1 - 1) / g.run1);
     } else {
         g.len1 = 0;
-        g.B_pitch = round_up(std::max<int64_t>(need, nt + p->max_extent), g.tt1);
+        const int64_t least = std::max<int64_t>(need, nt + p->max_extent);
+        g.B_pitch = round_up(mx_below ? std::max(least, pitch_mx) : least, g.tt1);
         g.n_ttiles1 = static_cast<int32_t>(g.B_pitch / g.tt1);
     }
     g.n_jchunks = (p->ngroups + g.J1 - 1) / g.J1;
