@@ -33,6 +33,10 @@ PEAK_ADD16 = 256 * 4 * 16 * 2 * 2.4e9   # 16-bit integer adds/s: 256 CUs x 64 la
 # 9-dword lane stride (4.12 clocks per wavefront read of 512 bytes).
 MEASURED_VOP3_PER_CLK_CU = 59.3
 MEASURED_PAIRED_LDS_B_PER_CLK_CU = 124.3
+# Additions/s of the matrix-core first stage where every product counts: one
+# 16x16x64 int8 MFMA (16 clocks on a SIMD at the dense int8 rate of 5.03e15
+# operations/s) adds 4 channels to 4 trials x 64 outputs.
+PEAK_MX_ADD = 256 * 4 * 2.4e9 / 16 * (4 * 4 * 64)
 PAPER_DM_SAMPLES_PER_S = 4096 / 153e-6  # real time on one CPU core, 4096 channels and trials, 153 us
 # HBM rates that tx_peaks measures on this part, the practical ceilings beside
 # the 8 TB/s published peak: a copy with 8 loads in flight per thread (bytes
@@ -83,6 +87,54 @@ def load_traffic(kernel, workload, split=False):
             return None
         return ent["read_bytes"], ent["write_bytes"]
     return ent.get("hbm_bytes_per_launch")
+
+
+def mx_windows(plan):
+    """Products per 4 channels and 4 trials that the matrix-core first stage
+    issues for the plan, against the one that a full product would need: the
+    16-byte windows that cover the trials' shifts beyond their smallest
+    (rounded down to 4 bytes), and the trials that fill up the last 16."""
+    i, t = plan.info, plan.tables()
+    g, nsub, m = i["ngroups"], i["nsub"], i["chans_per_sub"]
+    trials = np.minimum(np.arange((g + 15) // 16 * 16), g - 1)
+    d = t["coarse_chan"].reshape(g, nsub, m) - t["coarse_sub"][:, :, None]
+    d = d[trials].reshape(-1, 4, 4, nsub, m)                     # 16 trials, 4 trials
+    start = d.min(axis=(1, 2), keepdims=True) & ~15
+    base = (d.min(axis=2, keepdims=True) - start) & ~3
+    r = (d - start - base).max(axis=2)                           # per 4 trials and channel
+    r = np.pad(r, ((0, 0), (0, 0), (0, 0), (0, -m % 4))).reshape(*r.shape[:3], -1, 4).max(axis=-1)
+    return float((1 + (r + 7) // 16).sum()) * 16 / (g * nsub * m)
+
+
+def stage1_roofline(tx, plan, nt, achieved):
+    """Bound, peak and loop ceilings of the first stage that the plan runs."""
+    outputs = tx.tx_tile_variants(1)[plan.resolved_tiles(nt)[0]][0]
+    if outputs % 256:
+        # Matrix-core form: its ceiling is the matrix cores' issue rate over
+        # the products it needs (the operand reads, xors and stores beside
+        # them are what it falls short by).
+        w = mx_windows(plan)
+        return {"bound": "mfma", "achieved": round(achieved, 3), "peak": round(PEAK_MX_ADD / 1e12, 3),
+                "unit": "Tadd/s", "frac": round(achieved * 1e12 / PEAK_MX_ADD, 4), "products_per_full_product": round(w, 4),
+                "loop_ceiling_Tadd_s": round(PEAK_MX_ADD / w / 1e12, 2), "loop_bound": "mfma",
+                "loop_ceiling_frac": round(achieved * 1e12 * w / PEAK_MX_ADD, 4)}
+    # General form.  Its inner loop, per 4 byte-adds of one channel: 3 VALU ops
+    # (byte align, byte permute, half of each of two 3-input adds) and
+    # (Q + 1) / Q 4-byte LDS reads issued as paired reads (Q = output dwords
+    # per lane of the tile variant in use).  Its two ceilings: 256 CUs x 4
+    # SIMDs x 16 lanes x 2.4 GHz lane-ops at 4/3 adds each, and paired LDS
+    # reads at the rate measured on this part.
+    q1 = outputs // 256
+    valu_ceiling = 256 * 4 * 16 * 2.4e9 * 4 / 3 / 1e12
+    valu_ceiling_measured = 256 * MEASURED_VOP3_PER_CLK_CU * 2.4e9 * 4 / 3 / 1e12
+    lds_ceiling = MEASURED_PAIRED_LDS_B_PER_CLK_CU * 256 * 2.4e9 / ((q1 + 1) / q1) / 1e12
+    loop_ceiling = min(valu_ceiling, lds_ceiling)
+    return {"bound": "alu", "achieved": round(achieved, 3), "peak": round(PEAK_ADD16 / 1e12, 3), "unit": "Tadd/s",
+            "frac": round(achieved * 1e12 / PEAK_ADD16, 4),
+            "loop_ceiling_Tadd_s": round(loop_ceiling, 2), "loop_bound": "valu" if valu_ceiling <= lds_ceiling else "lds",
+            "loop_ceiling_frac": round(achieved / loop_ceiling, 4),
+            "loop_ceiling_measured_Tadd_s": round(min(valu_ceiling_measured, lds_ceiling), 2),
+            "loop_ceiling_measured_frac": round(achieved / min(valu_ceiling_measured, lds_ceiling), 4)}
 
 
 def make_input(torch, plan, wl, synth, pitch):
@@ -800,28 +852,10 @@ def main():
     t1 = kern["stage1"]["avg_ms"] * 1e-3
     achieved = adds1 / t1 / 1e12
     traffic = load_traffic("stage1", args.workload)
-    # The first stage's inner loop, per 4 byte-adds of one channel: 3 VALU ops
-    # (byte align, byte permute, half of each of two 3-input adds) and
-    # (Q + 1) / Q 4-byte LDS reads issued as paired reads (Q = output dwords
-    # per lane of the tile variant in use).  Its two ceilings: 256 CUs x 4
-    # SIMDs x 16 lanes x 2.4 GHz lane-ops at 4/3 adds each, and paired LDS
-    # reads at the rate measured on this part.
-    q1 = tx.tx_tile_variants(1)[plan.resolved_tiles(nt)[0]][0] // 256
-    valu_ceiling = 256 * 4 * 16 * 2.4e9 * 4 / 3 / 1e12
-    valu_ceiling_measured = 256 * MEASURED_VOP3_PER_CLK_CU * 2.4e9 * 4 / 3 / 1e12
-    lds_ceiling = MEASURED_PAIRED_LDS_B_PER_CLK_CU * 256 * 2.4e9 / ((q1 + 1) / q1) / 1e12
-    loop_ceiling = min(valu_ceiling, lds_ceiling)
-    roofline = {"bound": "alu", "kernel": "stage1", "achieved": round(achieved, 3),
-                "peak": round(PEAK_ADD16 / 1e12, 3), "unit": "Tadd/s", "frac": round(achieved * 1e12 / PEAK_ADD16, 4),
-                "traffic": traffic,
+    roofline = {"kernel": "stage1", **stage1_roofline(tx, plan, nt, achieved), "traffic": traffic,
                 # HBM rate of the same launches (counter bytes / event time), against 8 TB/s
                 "hbm_GBps": None if traffic is None else round(traffic / t1 / 1e9, 1),
-                "hbm_frac": None if traffic is None else round(traffic / t1 / 8e12, 4),
-                "loop_ceiling_Tadd_s": round(loop_ceiling, 2),
-                "loop_bound": "valu" if valu_ceiling <= lds_ceiling else "lds",
-                "loop_ceiling_frac": round(achieved / loop_ceiling, 4),
-                "loop_ceiling_measured_Tadd_s": round(min(valu_ceiling_measured, lds_ceiling), 2),
-                "loop_ceiling_measured_frac": round(achieved / min(valu_ceiling_measured, lds_ceiling), 4)}
+                "hbm_frac": None if traffic is None else round(traffic / t1 / 8e12, 4)}
 
     # The other two kernels of the step against HBM: counter bytes per launch
     # (committed rocprofv3 summary, current source only) over event time.
