@@ -52,8 +52,9 @@ const char* tx_status_str(tx_status s);
 
 /* Return the scratch that libtx calls are done with on the current device to
  * the system (libtx keeps it for reuse otherwise: buffers of up to 64 MB, at
- * most 512 MB of them, and the device's stream-ordered pool).
- * Synchronises the device.  Errors: TX_EDEVICE. */
+ * most 512 MB of them, and the device's stream-ordered pool; a call that finds
+ * no memory left gives the buffers back by itself).  Synchronises the device.
+ * Errors: TX_EDEVICE. */
 tx_status tx_pool_trim(void);
 
 /* Version string of the library build. */
@@ -332,7 +333,7 @@ tx_status tx_norm_weights(const uint64_t* sums, int32_t nchan, int64_t nt, int32
 tx_status tx_dedisperse_norm(tx_plan_t plan, const uint8_t* d_in, int64_t in_pitch, int64_t nt,
                              const float* d_scale, const float* d_offset, float* d_out, int64_t out_pitch,
                              hipStream_t stream);
-/* Bytes of scratch tx_dedisperse_norm takes from the pool for nt outputs. */
+/* Bytes of scratch tx_dedisperse_norm takes for nt outputs. */
 tx_status tx_dedisperse_norm_ws_size(tx_plan_t plan, int64_t nt, int64_t* bytes);
 
 /* ------------------------------------------------------------------------ */
@@ -476,6 +477,11 @@ typedef struct tx_cand {
  * For each width the earliest t with the largest S is taken; the width with
  * the largest S/N wins, ties to the smaller width.  A row with var <= 0, or
  * with every width > nt, gives (0.0, widths[0], 0).
+ *
+ * Few long rows (at most 768, of at least 3 x 4096 samples) are split over
+ * workgroups, with scratch of at most 26 MB that comes as tx_dedisperse's; a
+ * call that gets none, and one under stream capture, takes none and gives the
+ * same result.  Other calls take no scratch.
  */
 tx_status tx_boxcar_snr(const int32_t* d_dmt, int32_t ndm, int64_t nt, int64_t pitch,
                         const int32_t* widths, int32_t nw,
@@ -494,6 +500,8 @@ tx_status tx_boxcar_snr(const int32_t* d_dmt, int32_t ndm, int64_t nt, int64_t p
  *                when it exceeds cap (only the first cap found are stored).
  *   d_snr, d_width, d_time  optional (NULL or all three): the per-row peaks
  *                of tx_boxcar_snr, computed in the same pass.
+ *
+ * Scratch as tx_boxcar_snr, for rows of more than 65536 samples only.
  */
 tx_status tx_candidates(const int32_t* d_dmt, int32_t ndm, int64_t nt, int64_t pitch,
                         const int32_t* widths, int32_t nw, double gamma,
@@ -555,7 +563,7 @@ tx_status tx_boxcar_snr_fixed(const float* d_dmt, int32_t ndm, int64_t nt, int64
  *   d_nclusters  device int64: C.
  *
  * Results are unique for the given points (no dependence on input order or
- * thread timing).  Scratch comes from the device's stream-ordered pool; the
+ * thread timing).  Scratch comes as tx_dedisperse's; the
  * call waits for its own work on `stream` before returning (its host-built
  * delay tables are copied on that stream).
  * Errors: TX_EINVAL, TX_ESTATE, TX_ENOMEM, TX_EDEVICE.

@@ -2,8 +2,9 @@
 // S/N over the boxcar widths, and the thresholded DM-time candidates
 // (Sec. 2.4, Eq. 5; Sec. 2.5).
 //
-// One workgroup per DM row (the batch form takes the rows of many jobs).  The
-// row is read from HBM once, in tiles of 4096 window starts:
+// One workgroup per DM row, several for few long rows (boxcar_scan_kernel); the
+// batch form takes the rows of many jobs.  The row is read from HBM once, in
+// tiles of 4096 window starts:
 //  * each tile's running sums (exclusive prefix, uint32: window sums are exact
 //    as differences) of its 4096 + longest-width samples go to LDS; the same
 //    loads accumulate the exact moments sum y and sum y^2 (uint64);
@@ -13,8 +14,9 @@
 //    up; the largest sum per (tile, width) is kept in LDS.
 // Then c = floor(sum/T), Q = sum y^2 - 2 c sum + T c^2 (= sum (y - c)^2, mod
 // 2^64), var = Q/T - (r/T)^2, sigma and 1/(sigma T) in float64 give the peak
-// S/N, and per width the least window sum S* whose S/N reaches gamma
-// (bisection with the same float64 expression).  Only tiles where some width's
+// S/N, and per width the least window sum S* whose S/N reaches gamma (the exact
+// solution checked against its neighbours with the same float64 expression, else
+// by bisection).  Only tiles where some width's
 // largest sum reaches its S* are read again to list candidates: a start is a
 // candidate when some width passes, and is reported with the width of highest
 // S/N.  Thread tid owns the starts t0 + tid + 256 j (j < 16).
@@ -200,8 +202,9 @@ __device__ __forceinline__ void scan_tile(const TX_GLOBAL int32_t* __restrict__ 
 // row's best, and not each wavefront with its own, leaves a quarter of the
 // lookups, and each costs about as much as a width's sums.  The widths are a
 // rolled loop, two a turn: a row's code is a third of the unrolled one's.
-// 4096 rows of 65536 samples, 10 widths: 521 us with lookups per wavefront and
-// unrolled widths, 365 so (1.07 GB: 2.9 TB/s); 96 rows of 1000003 samples, unsplit, 1340 and 950.
+// 4096 rows of 65536 samples, 10 widths: 514 us with lookups per wavefront and
+// unrolled widths, 343 so (1.07 GB: 3.1 TB/s); 203 rows of 5003 samples 34 and 18;
+// 96 rows of 1000003 samples, unsplit, 1340 and 950.
 template <int NWT, bool TAIL>
 __device__ __forceinline__ void peak_tile(const BoxcarArgs& a, BoxShared<NWT>& sh, int tile, int t0, int tid,
                                           bool keep_tmax) {
@@ -673,11 +676,10 @@ __device__ __forceinline__ void boxcar_row(const BoxcarArgs& a, int row, BoxShar
 
 #define TX_BOX_WAVES __attribute__((amdgpu_waves_per_eu(NWT <= 12 ? 7 : NWT <= 16 ? 6 : 5)))
 
-// Single job: one workgroup per row.
+// Single job: one workgroup per row.  62 VGPRs at every width count, so 7
+// waves per SIMD; the wave counts asked for (7, 6 from 13 widths, 5 from 17)
+// hold the batch form to them, which takes 72 VGPRs and else took 81.  Nothing spills.
 template <int NWT>
-// At least 5 waves per SIMD (at most 102 VGPRs).  When the kernel needed 113
-// VGPRs (4 waves) the cap made it 7% faster despite a 3-dword spill; the
-// current form needs 69 VGPRs with the cap (75 without) and spills nothing.
 __global__ __launch_bounds__(kThreads) TX_BOX_WAVES void boxcar_kernel(BoxcarArgs a) {
     __shared__ BoxShared<NWT> sh;
     const int row = static_cast<int>(blockIdx.x);        // grid = rows
@@ -691,9 +693,12 @@ __global__ __launch_bounds__(kThreads) TX_BOX_WAVES void boxcar_kernel(BoxcarArg
 // what it is with one lookup per wavefront and best and one atomic per 64
 // starts.  Of the values of 600 to 960 records (128 rows x 8192 samples) 55 to
 // 65% differ between two calls of this form, as many between this form and
-// one that also solves its thresholds by bisection, and 98% between this form and boxcar_kernel or
-// its candidate pass.  Larger calls, whose rows start as others end, and
-// batches, whose rows go to whichever workgroup is free, list in the faster form.
+// one that also solves its thresholds by bisection, and 98% between this form and
+// boxcar_kernel or its candidate pass.  That order costs time: with candidates in
+// every row and 10 widths 128 x 8192 take 78 us (boxcar_kernel 30), 512 x 16301 105 (49),
+// 256 x 61517 165 (split 71), 1280 x 65536 243 (145).  Longer rows, which a split
+// lists 6 times as fast, larger calls, whose rows start as others end, and
+// batches, whose rows go to whichever workgroup is free, list in the faster forms.
 template <int NWT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void boxcar_list_kernel(BoxcarArgs a) {
     __shared__ BoxShared<NWT> sh;
@@ -875,12 +880,11 @@ static BoxFns box_fns(int nwt) {
 // Split of a row's tiles over workgroups (parts 1: none): as far as 6
 // workgroups per CU, where they still run side by side at little cost, but
 // parts of at least 1 + rows / 128 tiles, and only rows of 3 such parts: the
-// second launch costs about 10 us, a tile 4 us on an idle CU and more on a
-// full one.  Measured unsplit and split (10 widths, candidates in
-// every row): 96 x 1000003 samples 950 and 154 us, 128 x 28749 60 and 41,
-// 256 x 61517 97 and 67, 512 x 61517 114 and 87, 512 x 245837 400 and 253;
-// without the limits 512 x 12365 46 and 63, 768 x 61517 130 and 132, 1024 x 61517
-// 149 and 180.
+// second launch costs 6 to 10 us, a tile 4 us on an idle CU and more on a
+// full one.  Measured unsplit and split (10 widths, peaks): 96 x 1000003
+// samples 1009 and 145 us, 128 x 28749 40 and 32, 256 x 61517 71 and 52,
+// 512 x 61517 77 and 66, 512 x 245837 283 and 182; without the limits
+// 512 x 12365 28 and 39, 768 x 61517 88 and 91, 1024 x 61517 100 and 101.
 static BoxSplit box_split(int rows, int ntiles, int nwt) {
     const int unit = 1 + rows / 128;
     const int parts = ntiles >= 3 * unit ? std::min({ntiles / unit, 64, kSplitGroups / rows}) : 1;

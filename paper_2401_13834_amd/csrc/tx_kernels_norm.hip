@@ -509,11 +509,10 @@ __global__ __launch_bounds__(kThreads) void stage2_norm_kernel(Stage2NormArgs a)
 //    squares of the row;
 //  * for a fixed width the S/N is a non-decreasing function of the window
 //    sum, so the per-width peak is found on the sums alone: every lane keeps
-//    the largest sum of its starts per width, the wavefront's largest is
-//    compared with the wavefront's best so far, and only when it beats it (a
-//    few tiles per row) does the wavefront look up the earliest start
-//    reaching it; each wavefront's largest sums per (tile, width) are kept in
-//    LDS where they fit.
+//    the largest sum of its starts per width, the tile's largest is compared
+//    with the row's best so far, and only when it beats it (a few tiles per
+//    row) is the earliest start reaching it looked up; the tile's largest sums
+//    per width are kept in LDS where they fit.
 // Then the mean and sigma give each width's peak S/N (the largest over widths,
 // ties to the smaller width), and per width S*, the least float64 sum whose
 // S/N (the same float64 expression) reaches gamma, by bisection over the
@@ -678,8 +677,8 @@ __device__ __forceinline__ void norm_scan_tile(const TX_GLOBAL float* __restrict
 // the tile beats the row's best sum of a width (a few tiles per row), the
 // wavefronts that hold that sum look up its earliest start.  Comparing with
 // the whole row's best, and not each wavefront with its own, leaves a quarter
-// of the lookups.  4096 rows of 65536 samples, 8 widths: 867 us with lookups
-// per wavefront and unrolled widths, 701 so; 168 rows of 5003 samples 35 and 23.
+// of the lookups.  4096 rows of 65536 samples, 10 widths: 963 us with lookups
+// per wavefront and unrolled widths, 744 so; 168 rows of 5003 samples 39 and 23.
 // TAIL: some windows reach past the row end (they count as -inf).
 template <int NWT, bool TAIL>
 __device__ __forceinline__ void norm_peak_tile(NormBoxShared<NWT>& sh, int T, int t0, int tid, double* tmax) {

@@ -35,7 +35,8 @@ __device__ __forceinline__ int dpp_move(int v) {
 // same registers, and every other 4 outputs take the window 8 bytes on.
 // Trials spread over more than the 16 bytes allow are covered by further
 // windows 16 bytes on (nwin; 1.24 on average on the 4096-channel block with
-// DM steps of 0.5).  Samples are made signed (x - 128); the accumulators
+// DM steps of 0.5, bases being rounded down to 4 bytes: the spreads alone, which
+// the plan's estimate takes, need 1.18).  Samples are made signed (x - 128); the accumulators
 // start at 128 m.
 //
 // Workgroup = (sub-band, 16 coarse trials, a run of tiles of TT = 64 QN
@@ -49,10 +50,10 @@ __device__ __forceinline__ int dpp_move(int v) {
 //
 // A lane reads 4 (1 + 2 / QN) bytes of LDS per 4 trials x 4 outputs (the
 // general form: 16 (1 + 1 / Q)), and its VALU work is one xor per such dword.
-// Bound by instruction issue: on the 4096-channel, 4096-trial block (8.5e10
-// additions) the matrix cores are busy 0.80 of 1.7 ms at the 2.05 GHz the chip
-// then runs at, and the same kernel without its loads and stores takes 1.4 ms;
-// the general form takes 2.4 ms.  Measured choices: QN = 18 (114 registers, 4
+// Bound by the SIMDs' issue: on the 4096-channel, 4096-trial block (8.5e10
+// additions) the matrix cores are busy 0.80 of 1.7 ms (43% of the clocks, counted; 2.05 GHz),
+// and beside every MFMA of 16 clocks go 3.2 other VALU, 0.9 LDS and 3.0 scalar
+// instructions; the general form takes 2.4 ms.  Measured choices: QN = 18 (114 registers, 4
 // workgroups per CU) 1.71, 10 1.88, 26 1.94, 34 1.95 ms; exact 1-byte bases
 // (v_alignbyte on every operand dword, 8% fewer windows) 2.05; making samples
 // signed in LDS 1.95; the next window's samples read ahead 2.0 (128 registers
